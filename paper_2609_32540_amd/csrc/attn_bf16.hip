@@ -67,23 +67,11 @@
 
 #include <utility>
 
+#include "attn_tile.h"
 #include "ff_internal.h"
 
 namespace ff {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-
-#define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
-#define GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
 
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
@@ -92,6 +80,7 @@ constexpr int kWaveQ = 16 * kQH;            // queries per wave
 constexpr int kBlockQ = kWaves * kWaveQ;    // queries per workgroup
 constexpr int kBK = 64;                     // keys per tile
 constexpr int kXcds = 8;
+constexpr int kCus = 256;                   // workgroups of one round (one per CU)
 constexpr float kSumLimit = 16.0f;          // checked pass: largest block sum of probabilities kept
 constexpr float kFastLimit = 0x1p64f;       // fast pass: largest row sum before the checked pass
 // passes of the key loop
@@ -121,64 +110,6 @@ struct Cfg {
   static constexpr int KGB = D / 32;         // 1 KB blocks per 16-row group of a K tile
   static_assert(BLOCKS % kCopyWaves == 0, "every copying wave copies the same number of 1 KB blocks");
 };
-
-// N 1 KB copies from global memory straight into LDS: copy i takes 16 bytes
-// per lane from base + off[i] + 1024 i into LDS at dst + 1024 i + 16 lane.  The
-// instruction's immediate offset moves both addresses, so m0 (the LDS base) is
-// written once for all N; callers fold -1024 i into off[i] and lower base by
-// 1024 (N - 1) so that every per-lane offset stays non-negative.  Written out so
-// that the compiler does not track these copies: their completion is waited
-// for explicitly (vmcnt) before the barrier that hands a tile to the other
-// waves.
-template <int N>
-__device__ inline void lds_copy_blocks(uint32_t dst, const char* base, const uint32_t (&off)[N]) {
-  static_assert(N == 2 || N == 4, "two or four 1 KB copies per wave and tensor");
-  if constexpr (N == 2)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %1, %3\n\t"
-                 "global_load_lds_dwordx4 %2, %3 offset:1024"
-                 :: "s"(dst), "v"(off[0]), "v"(off[1]), "s"(base) : "memory");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %1, %5\n\t"
-                 "global_load_lds_dwordx4 %2, %5 offset:1024\n\t"
-                 "global_load_lds_dwordx4 %3, %5 offset:2048\n\t"
-                 "global_load_lds_dwordx4 %4, %5 offset:3072"
-                 :: "s"(dst), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory");
-}
-
-__device__ inline uint32_t pack_bf16(float a, float b) {
-  f32x2 f = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
-}
-
-// max and sum over the lanes n, n + 16, n + 32, n + 48 (the four lane groups
-// holding one query's keys)
-__device__ inline float max_across_groups(float x) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const float y = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-__device__ inline float sum_across_groups(float x) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const float y = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// 64-bit value of lane `lane` (wave-uniform index).  The builtin works on
-// signed 32-bit words: each half is widened as unsigned, so a low word with
-// its top bit set does not sign-extend into the high word.
-__device__ inline uint64_t readlane_u64(uint64_t v, int lane) {
-  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v)), lane));
-  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v >> 32)), lane));
-  return (uint64_t(hi) << 32) | uint64_t(lo);
-}
-
-// s_waitcnt immediate: vmcnt = vm; lgkmcnt and expcnt not waited for
-constexpr int waitcnt_vm(int vm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | (15 << 8); }
 
 // Instruction order of one half of a pipeline step, by sched_group_barrier
 // classes (0x008 matrix, 0x100 LDS read, 0x002 VALU, 0x400 transcendental):
@@ -810,6 +741,21 @@ __global__ __launch_bounds__(256) void tail_merge_kernel(const float* __restrict
   *reinterpret_cast<u32x4*>(out + (int64_t(qi) * heads + head) * D + 8 * ch) = w4;
 }
 
+// Key tiles of a launch with several read sets.  The GPU takes its workgroups as
+// CUs come free, so the busiest CU walks at least an even share of all tiles
+// and the longest set.
+struct SetTiles {
+  double sum = 0.0, most = 0.0;
+  int sets = 0;
+  void add(int tiles) {
+    sum += tiles;
+    most = tiles > most ? tiles : most;
+    ++sets;
+  }
+  double mean() const { return sum / sets; }
+  double whole(unsigned workgroups) const { return fmax(most, mean() * workgroups / kCus); }
+};
+
 }  // namespace
 
 int attention_bf16_units(int nq, int heads) { return heads * ((nq + kBlockQ - 1) / kBlockQ); }
@@ -831,6 +777,12 @@ hipError_t launch_attention_bf16(const void* q, void* out, int nq, int heads, in
   const int n_qtiles = (nq + kBlockQ - 1) / kBlockQ;
   const int units = n_qtiles * heads;
   const int n_tail = units - tail.n_full;
+  const double rounds = double((tail.n_full + kCus - 1) / kCus) +
+                        (n_tail > 0 ? double((n_tail * tail.split + kCus - 1) / kCus) / tail.split : 0.0);
+  const int tiles = attention_bf16_key_tiles(segs);
+  if (const int qt = attention_bf16_split_tiles(nq, heads, head_dim, 1, tiles, tiles, rounds * tiles,
+                                                n_tail > 0))
+    return launch_attention_bf16_split(qt, q, out, nq, heads, head_dim, softmax_scale, segs, stream);
   const dim3 grid(tail.n_full + n_tail * tail.split);
   const float scale_log2 = float(double(softmax_scale) * 1.4426950408889634);
   if (head_dim == 128)
@@ -859,6 +811,11 @@ hipError_t launch_attention_bf16_batch(int nq, int heads, int head_dim, float so
   if (nq <= 0 || b.n <= 0) return hipSuccess;
   const int n_qtiles = (nq + kBlockQ - 1) / kBlockQ;
   const dim3 grid(b.n * n_qtiles * heads);
+  SetTiles t;
+  for (int j = 0; j < b.n; ++j) t.add(attention_bf16_key_tiles(b.set[j]));
+  if (const int qt = attention_bf16_split_tiles(nq, heads, head_dim, b.n, t.mean(), t.most,
+                                                t.whole(grid.x), false))
+    return launch_attention_bf16_split_batch(qt, nq, heads, head_dim, softmax_scale, b, stream);
   const float scale_log2 = float(double(softmax_scale) * 1.4426950408889634);
   const TailSplit whole = {int(grid.x), 1, nullptr};
   if (head_dim == 128)
@@ -877,6 +834,16 @@ hipError_t launch_attention_bf16_packed(const void* q, void* out, int heads, int
   if (nq <= 0 || plan.n_chunks <= 0) return hipSuccess;
   const int n_qtiles = (nq + kBlockQ - 1) / kBlockQ;
   const dim3 grid(plan.n_chunks * n_qtiles * heads);
+  SetTiles t;
+  for (int c = 0; c < plan.n_chunks; ++c) {
+    int n = 0;
+    for (int i = 0; i < packed_num_segments(plan, c); ++i)
+      n += (packed_segment(plan, c, i, heads, head_dim, 2).len + kBK - 1) / kBK;
+    t.add(n);
+  }
+  if (const int qt = attention_bf16_split_tiles(nq, heads, head_dim, plan.n_chunks, t.mean(), t.most,
+                                                t.whole(grid.x), false))
+    return launch_attention_bf16_split_packed(qt, q, out, heads, head_dim, softmax_scale, plan, stream);
   const float scale_log2 = float(double(softmax_scale) * 1.4426950408889634);
   const TailSplit whole = {int(grid.x), 1, nullptr};
   if (head_dim == 128)

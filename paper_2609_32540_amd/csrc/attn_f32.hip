@@ -37,32 +37,16 @@
 
 #include <math.h>
 
+#include "attn_tile.h"
 #include "ff_internal.h"
 
 namespace ff {
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kWaves = 8;                 // key groups of a workgroup
 constexpr int kThreads = 64 * kWaves;
 constexpr int kBK = 16;                   // keys per block
 constexpr int kXcds = 8;
-
-// max / sum over the lanes n, n + 16, n + 32, n + 48 (one query's four key groups)
-__device__ inline float max_across_groups(float x) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const float y = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-__device__ inline float sum_across_groups(float x) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const float y = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 
 template <int D, int QT, class Src>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))

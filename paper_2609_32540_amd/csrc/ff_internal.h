@@ -154,6 +154,28 @@ hipError_t launch_attention_f32_packed(const void* q, void* out, int heads, int 
                                        float softmax_scale, const PackedPlan& plan,
                                        hipStream_t stream);
 
+// bf16 launches whose waves split the keys instead of the queries
+// (attn_bf16_split.hip), for launches too small to fill the GPU with
+// 256-query workgroups.  Returns the 16-query tiles per workgroup to launch them
+// with, or 0 where the 256-query kernel is the better one.  tiles_mean and
+// tiles_max: 64-key tiles of the launch's read sets; whole_tiles: the tiles that
+// the busiest CU would walk in the 256-query kernel; merged: whether that would
+// need the merge kernel.
+int attention_bf16_split_tiles(int nq, int heads, int head_dim, int sets, double tiles_mean,
+                               double tiles_max, double whole_tiles, bool merged);
+
+hipError_t launch_attention_bf16_split(int qt, const void* q, void* out, int nq, int heads,
+                                       int head_dim, float softmax_scale, const KvSegments& segs,
+                                       hipStream_t stream);
+
+hipError_t launch_attention_bf16_split_batch(int qt, int nq, int heads, int head_dim,
+                                             float softmax_scale, const KvBatch& b,
+                                             hipStream_t stream);
+
+hipError_t launch_attention_bf16_split_packed(int qt, const void* q, void* out, int heads,
+                                              int head_dim, float softmax_scale,
+                                              const PackedPlan& plan, hipStream_t stream);
+
 // Backward pass of a packed launch (bf16): delta (workspace, [rows][heads]
 // f32) = dO . O, then dQ, dV and dK; frame_runs[f] lists the (first chunk,
 // count) runs of chunks that see anchor frame f.

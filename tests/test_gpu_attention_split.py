@@ -1,0 +1,109 @@
+"""GPU parity of the key-split bf16 attention kernel (small launches) at the edges of its
+tiling: 16- and 32-query workgroups, 32-key blocks dealt over eight waves, read sets with
+fewer blocks than waves, segments that end inside a block; single, batched and packed
+launches (the packed one with its log-sum-exp).  Bars of the bf16 path: max-abs 2e-2 and
+relative-L2 5e-3 of float64 per call; log-sum-exp within 1e-4 (float32 sums of at most 300
+probabilities, each with a relative error of a few 2^-24 times the score's magnitude)."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import ff_oracle as fo
+from paper_2609_32540_amd import ff
+
+from gpu_util import PairedRun, check_attention, exact, make_cache, make_oracle, to_dev
+from test_gpu_packed import clip, oracle_packed
+from test_gpu_parity import small
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True, scope="module")
+def _needs_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    ff.lib()
+
+
+# chunk tokens 3, 15, 18, 33 and 99 (16-query workgroups), and 351 with 24 heads (528
+# workgroups of one tile are three rounds: two tiles a workgroup, the last ragged)
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("heads,grid", [(1, (1, 1)), (2, (1, 5)), (2, (2, 3)), (3, (1, 11)), (3, (3, 11)),
+                                        (24, (9, 13))])
+def test_tiles_and_blocks(head_dim, heads, grid):
+    w = small("bf16", head_dim, heads=heads, grid_h=grid[0], grid_w=grid[1], stages=1, layers=1,
+              n_chunks=4)
+    run = PairedRun(w, rope=False)
+    for c in range(w.n_chunks):
+        run.step(c, 0, 0)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_rising_scores(head_dim):
+    # keys of later chunks scaled by 3^c: the reference max is raised again and again
+    w = small("bf16", head_dim, grid_h=3, grid_w=7, stages=1, layers=1, n_chunks=4)
+    cache, oracle = make_cache(w, 1, 1), make_oracle(w, 1, 1)
+    for c in range(w.n_chunks):
+        q, k, v = (synth.chunk_tensor(w, t, c, 0, 0) for t in (synth.T_Q, synth.T_K, synth.T_V))
+        k = (k.float() * 3.0 ** c).to(k.dtype)
+        out = cache.chunk_attention(0, 0, c, to_dev(q), to_dev(k), to_dev(v))
+        check_attention(exact(out), oracle.attention(0, 0, c, exact(q), exact(k), exact(v)), "bf16",
+                        f"chunk {c}")
+        cache.kv_publish(0, 0, c, to_dev(k), to_dev(v))
+        oracle.publish(0, 0, c, exact(k), exact(v))
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_batch_items_of_different_lengths(head_dim):
+    w = small("bf16", head_dim, grid_h=5, grid_w=7, ring_chunks=3, stages=3, layers=1, n_chunks=3)
+    cache, oracle = make_cache(w, 3, 1), make_oracle(w, 3, 1)
+    items = []
+    for s in range(3):     # stage s holds s chunks
+        for c in range(s + 1):
+            q, k, v = (to_dev(synth.chunk_tensor(w, t, c, s, 0)) for t in (synth.T_Q, synth.T_K, synth.T_V))
+            if c < s:
+                cache.kv_publish(s, 0, c, k, v)
+                oracle.publish(s, 0, c, exact(k), exact(v))
+        items.append(dict(stage=s, layer=0, chunk=s, q=q, k=k, v=v))
+    for s, (it, out) in enumerate(zip(items, cache.chunk_attention_batch(items))):
+        ref = oracle.attention(s, 0, s, exact(it["q"]), exact(it["k"]), exact(it["v"]))
+        check_attention(exact(out), ref, "bf16", f"stage {s}")
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("grid", [(1, 1), (3, 5), (5, 7)])
+def test_packed_with_log_sum_exp(head_dim, grid):
+    w = small("bf16", head_dim, grid_h=grid[0], grid_w=grid[1], stages=1, layers=1, n_chunks=4)
+    n, G = 4, w.tokens_per_frame
+    q, k, v = (to_dev(t) for t in clip(w, n))
+    ak, av = (to_dev(t) for t in synth.anchor_tensors(w, [0, 1, 2], 0))
+    table = [[0], [2, 0], [], [0, 1, 2]]
+    lse = torch.empty(q.shape[:2], dtype=torch.float32, device=q.device)
+    scale = 1.0 / math.sqrt(head_dim)
+    out = ff.packed_attention(q, k, v, n_chunks=n, window=1, anchor_k=ak, anchor_v=av, frame_tokens=G,
+                              anchors_of_chunk=table, lse=lse)
+    ref = oracle_packed(w, q, k, v, ak, av, table, 1, scale)
+    nq = w.chunk_tokens
+    for c in range(n):
+        check_attention(exact(out[c * nq:(c + 1) * nq]), ref[c], "bf16", f"chunk {c}")
+        keys = [exact(ak[f * G:(f + 1) * G]) for f in table[c]] + [exact(k[max(0, c - 1) * nq:(c + 1) * nq])]
+        keys = np.concatenate(keys)
+        want = fo.log2_sum_exp2(exact(q[c * nq:(c + 1) * nq]), keys, np.ones((nq, len(keys)), bool), scale)
+        np.testing.assert_allclose(exact(lse[c * nq:(c + 1) * nq]), want, atol=1e-4)
+
+
+# the smallest launches left to the 256-query kernel, whose partial last round runs as 2, 3
+# and 4 key parts: 96, 80 and 60 units on 256 CUs
+@pytest.mark.parametrize("heads,grid,head_dim", [(24, (12, 22), 128), (24, (12, 22), 64),
+                                                 (40, (9, 13), 128), (12, (15, 26), 128),
+                                                 (12, (15, 26), 64)])
+def test_key_parts_of_the_256_query_kernel(heads, grid, head_dim):
+    w = small("bf16", head_dim, heads=heads, grid_h=grid[0], grid_w=grid[1], ring_chunks=5, stages=1,
+              layers=1, n_chunks=6)
+    run = PairedRun(w, rope=False)
+    rows = np.r_[0:40, w.chunk_tokens - 40:w.chunk_tokens]
+    for c in range(w.n_chunks):
+        run.step(c, 0, 0, check=c >= 4, heads=[0, heads - 1], rows=rows)

@@ -811,6 +811,71 @@ void bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ dou
   }
 }
 
+// Stationary 16-row tiles per workgroup of the split kernels (attn_bwd_split.hip),
+// or 0 where the 256-row kernels of this file are the better ones: the shortest
+// estimate, per pass, of a fixed part plus the 64-row tiles that the busiest CU
+// streams (an even share of all and a third of the longest stream, at least the
+// longest one) times the time of one.  The constants are fits to 30 launches of
+// 1 to 40 heads, 3 to 27 chunks of 63 to 2016 tokens, each form forced (us of
+// the whole backward, 256-row kernels / split dQ / split dK and dV: 6 heads x 64,
+// 7 chunks of 351 tokens 119 / 98 / 78; 1 head x 128, 18 x 432 386 / 328 / 143;
+// 24 heads x 128, 11 x 1056, which fills the GPU, 2479 / 2551 / 2743).
+struct SplitChoice {
+  int q, k;   // dQ; dK and dV
+};
+
+SplitChoice choose_split(const PackedPlan& plan, int heads, int head_dim, const KeyUnits& ku) {
+  struct Cost { double fixed, tile; };   // us, us per 64-row tile
+  struct Load {
+    double sum = 0.0, most = 0.0;        // tiles of all workgroups, of the longest
+    void add(double tiles, double workgroups) {
+      sum += tiles * workgroups;
+      most = fmax(most, tiles);
+    }
+    double us(const Cost& c) const { return c.fixed + c.tile * fmax(most, sum / 256.0 + 0.35 * most); }
+  };
+  constexpr double kMargin = 0.92;   // near a tie the 256-row kernels, which read less
+  const bool wide = head_dim == 128;
+  const Cost cost_q[3] = {wide ? Cost{4.0, 2.93} : Cost{4.0, 1.89}, wide ? Cost{4.5, 0.46} : Cost{8.0, 0.25},
+                          wide ? Cost{4.5, 0.68} : Cost{8.0, 0.37}};
+  const Cost cost_k[3] = {wide ? Cost{4.0, 3.33} : Cost{8.0, 1.64}, wide ? Cost{4.0, 0.49} : Cost{10.0, 0.27},
+                          wide ? Cost{4.0, 0.49} : Cost{10.0, 0.32}};
+  const int nq = plan.chunk_tokens, n = plan.n_chunks;
+  const int window = plan.window < n ? plan.window : n;
+  const auto groups = [](int rows, int per) { return double((rows + per - 1) / per); };
+  SplitChoice choice = {0, 0};
+  double best_q = 0.0, best_k = 0.0;
+  for (int t = 0; t <= 2; ++t) {
+    const int per = t == 0 ? kBlockN : 16 * t;
+    Load lq, lk;
+    for (int c = 0; c < n; ++c) {
+      double tiles = 0.0;
+      for (int i = 0; i < packed_num_segments(plan, c); ++i)
+        tiles += groups(packed_segment(plan, c, i, heads, head_dim, 2).len, kBT);
+      lq.add(tiles, groups(nq, per) * heads);
+      lk.add(groups(((c + window < n - 1 ? c + window : n - 1) - c + 1) * nq, kBT),
+             groups(nq, per) * heads);
+    }
+    for (int f = 0; f < ku.n_frames; ++f) {
+      double tiles = 0.0;
+      for (int r = 0; r < 8; ++r) tiles += groups(ku.frame_runs[f][2 * r + 1] * nq, kBT);
+      lk.add(tiles, groups(plan.frame_tokens, per) * heads);
+    }
+    const double margin = t == 0 ? kMargin : 1.0;
+    const double us_q = margin * lq.us(cost_q[t]), us_k = margin * lk.us(cost_k[t]);
+    if (t == 0 || us_q < best_q) {
+      best_q = us_q;
+      choice.q = t;
+    }
+    if (wide && t == 2) continue;   // dK and dV take one tile at d = 128
+    if (t == 0 || us_k < best_k) {
+      best_k = us_k;
+      choice.k = t;
+    }
+  }
+  return choice;
+}
+
 }  // namespace
 
 hipError_t launch_attention_bwd_bf16(const void* q, const void* out, const void* dout,
@@ -846,18 +911,30 @@ hipError_t launch_attention_bwd_bf16(const void* q, const void* out, const void*
   const __bf16* dp = static_cast<const __bf16*>(dout);
   __bf16 *dkp = static_cast<__bf16*>(dk), *dvp = static_cast<__bf16*>(dv);
   __bf16 *dakp = static_cast<__bf16*>(dak), *davp = static_cast<__bf16*>(dav);
+  const SplitChoice split = choose_split(plan, heads, head_dim, ku);
   // Rings (LDS: 160 KB per workgroup): d = 128 dQ fits three 32 KB slots beside its 64 KB
   // dO stash; the d = 128 dK/dV pass (V stash plus the streamed vectors) four slots of
   // 32-row tiles, which also keeps the per-block registers within two waves per SIMD
   // beside both accumulators; d = 64 takes four 64-row slots in both passes.
-  if (head_dim == 128) {
+  if (split.q) {
+    const hipError_t e = launch_bwd_split_dq(split.q, q, dout, lse, delta, dq, heads, head_dim,
+                                             softmax_scale, plan, stream);
+    if (e != hipSuccess) return e;
+  } else if (head_dim == 128) {
     hipLaunchKernelGGL((bwd_dq_kernel<128, 3>), g_q, dim3(kThreads), 0, stream, qp, dp, lse, delta,
                        static_cast<__bf16*>(dq), heads, c_log2, softmax_scale, plan, n_qtiles);
-    hipLaunchKernelGGL((bwd_dkv_kernel<128, 4, 32>), g_k, dim3(kThreads), 0, stream, qp, dp, lse,
-                       delta, dkp, dakp, dvp, davp, heads, c_log2, softmax_scale, plan, ku);
   } else {
     hipLaunchKernelGGL((bwd_dq_kernel<64, 4>), g_q, dim3(kThreads), 0, stream, qp, dp, lse, delta,
                        static_cast<__bf16*>(dq), heads, c_log2, softmax_scale, plan, n_qtiles);
+  }
+  if (split.k) {
+    const hipError_t e = launch_bwd_split_dkv(split.k, q, dout, lse, delta, dk, dv, dak, dav, heads,
+                                              head_dim, softmax_scale, plan, frame_runs, n_frames, stream);
+    if (e != hipSuccess) return e;
+  } else if (head_dim == 128) {
+    hipLaunchKernelGGL((bwd_dkv_kernel<128, 4, 32>), g_k, dim3(kThreads), 0, stream, qp, dp, lse,
+                       delta, dkp, dakp, dvp, davp, heads, c_log2, softmax_scale, plan, ku);
+  } else {
     hipLaunchKernelGGL((bwd_dkv_kernel<64, 4, 64>), g_k, dim3(kThreads), 0, stream, qp, dp, lse,
                        delta, dkp, dakp, dvp, davp, heads, c_log2, softmax_scale, plan, ku);
   }

@@ -186,6 +186,18 @@ hipError_t launch_attention_bwd_bf16(const void* q, const void* out, const void*
                                      const uint8_t (*frame_runs)[16], int n_frames,
                                      hipStream_t stream);
 
+// dQ, and dK and dV, of launches too small to fill the GPU with the 256-row
+// workgroups of launch_attention_bwd_bf16 (attn_bwd_split.hip), which chooses
+// them; tiles: 16-row tiles per workgroup (1 or 2).
+hipError_t launch_bwd_split_dq(int tiles, const void* q, const void* dout, const float* lse,
+                               const float* delta, void* dq, int heads, int head_dim,
+                               float softmax_scale, const PackedPlan& plan, hipStream_t stream);
+
+hipError_t launch_bwd_split_dkv(int tiles, const void* q, const void* dout, const float* lse,
+                                const float* delta, void* dk, void* dv, void* dak, void* dav,
+                                int heads, int head_dim, float softmax_scale, const PackedPlan& plan,
+                                const uint8_t (*frame_runs)[16], int n_frames, hipStream_t stream);
+
 // Euler step x_out = x - dsigma * v over n elements of dtype (x_out may be x).
 hipError_t launch_euler(const void* x, const void* v, void* y, int64_t n, double dsigma,
                         int dtype, hipStream_t stream);

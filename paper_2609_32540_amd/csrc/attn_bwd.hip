@@ -11,443 +11,171 @@
 // one chunk and head and streams the 64-key tiles of their read set, like the
 // forward); dK and dV together (key-stationary: a workgroup holds 256 keys of
 // one chunk or anchor frame and head and streams the query tiles of every
-// chunk that sees them, 32 rows per tile at d = 128, 64 at d = 64).  Every
-// output element is written by exactly one workgroup: no atomics.
+// chunk that sees them).  Every output element is written by exactly one
+// workgroup: no atomics.  Launches too small to fill the GPU with these run the
+// kernels of attn_bwd_split.hip (choose_split).
 //
-// Products on v_mfma_f32_32x32x16_bf16 with the forward's operand layouts: the
-// stationary side (Q^T and dO^T, or K^T and V^T) sits in registers as the B
-// operand (the second one, where registers run out, in a swizzled LDS copy),
-// tiles of the streamed side are copied HBM -> LDS (global_load_lds) ahead of
-// use into a ring of two to four slots and read as the A operand (16-byte
-// rows) or, transposed, with ds_read_b64_tr_b16; P and dS go from the
-// accumulators to the B operand of the next product as bf16 (nearest even).
-// With three or more slots the two waves of each SIMD work half a tile apart,
-// as in the forward kernel (see Ring).
+// Both kernels are bound by the matrix cores and the power they draw.  Products
+// on v_mfma_f32_16x16x32_bf16 (the bf16 shape with the least register traffic
+// per FLOP) with the forward's operand layouts: the stationary side sits in
+// registers as the B operand (V of the dK/dV kernel, where they run out, in
+// LDS), tiles of the streamed side are copied HBM -> LDS (global_load_lds) into
+// a ring of five slots and read as the A operand by rows (16 bytes) or
+// transposed (ds_read_b64_tr_b16); P and dS go from the accumulators to the B
+// operand of the next product as bf16 (nearest even).  Against the 32x32x16
+// kernels before them, at 12 heads x 128, 27 chunks of 4680 tokens (one box,
+// whole training step 86.2 ms -> 77.9 ms): dQ with dO in LDS, products and VALU
+// work in sequence 28.8 ms -> 25.2 ms; dK and dV 38.5 ms -> 34.0 ms, of which the
+// operands read one region ahead give 1.6 ms and waves without rows, which skip
+// the products of a ragged last tile, 0.8 ms together.
 
 #include <hip/hip_runtime.h>
 
 #include <math.h>
 
 #include <cstring>
+#include <utility>
 
+#include "attn_tile.h"
 #include "ff_internal.h"
 
 namespace ff {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-#define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
-#define GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
-
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kBlockN = 32 * kWaves;   // stationary columns (queries or keys) per workgroup
-constexpr int kBT = 64;                // streamed rows per tile (32 in the d = 128 dK/dV pass)
+constexpr int kBT = 64;                // streamed rows per tile (32 in the dK/dV kernel at d = 128)
 constexpr int kXcds = 8;
 constexpr int kMaxRuns = 2 * FF_MAX_ANCHOR_FRAMES + 1;   // segments of one streamed set
 
-template <int D, int BT = kBT>
-struct Cfg {
-  static constexpr int KS = D / 16;
-  static constexpr int DB = D / 32;
+template <int D, int kRows>
+struct Tile {
+  static constexpr int KS = D / 32;                // 32-wide d slices
+  static constexpr int DT = D / 16;                // 16-row d tiles of a gradient
   static constexpr int ROWB = 2 * D;
-  static constexpr int CPR = D / 8;
-  static constexpr int RPB = 1024 / ROWB;
-  static constexpr int BLOCKS = BT / RPB;               // 1 KB copies per tile and tensor
-  static constexpr int TILE = BT * ROWB;
-  static constexpr int VEC = BT * 4;                    // one float per streamed row
-  static_assert(BLOCKS % kWaves == 0, "every wave copies the same number of 1 KB blocks");
+  static constexpr int TILE = kRows * ROWB;
+  static constexpr int SLOT = 2 * TILE;            // the tiles of the two streamed tensors
+  // Waves w and w + 4 share a SIMD and the older one (w < 4) is favoured by the
+  // issue arbiter: waves 0-3 make the tile copies.
+  static constexpr int kCopyWaves = kWaves / 2;
+  static constexpr int N = TILE / 1024 / kCopyWaves;   // 1 KB copies per copying wave and tensor
+  static constexpr int VGB = D / 64;               // 1 KB blocks per 8-row group
 };
 
-// Ring schedules.  NS = 2: all eight waves copy tile t+1 after barrier t and
-// then work on tile t in lock step.  NS >= 3: waves 0-3 copy tile t + NS - 2
-// after barrier t (before their blocks with three slots, after them with
-// four) and run both 32-row blocks of tile t; their SIMD partners,
-// waves 4-7, run block 1 of tile t-1 and then block 0 of tile t, half a tile
-// later, so one wave's exponentials meet the other's matrix work.  Tile u
-// sits in slot u % NS; its last reads (block 1 by waves 4-7) precede barrier
-// u+2, and its slot is refilled at barrier u + 2 at the earliest.
-template <int NS>
-struct Ring {
-  static_assert(NS >= 2 && NS <= 4, "two to four slots");
-  static constexpr bool kOffset = NS >= 3;
-  static constexpr int kCopyWaves = kOffset ? kWaves / 2 : kWaves;
-  static constexpr int kAhead = kOffset ? NS - 2 : 1;   // tiles copied ahead of the first reader
-};
+// Streamed tiles are read by rows and transposed: a tile is d-blocked per 8 rows
+// (one 256-byte line per 16-wide d tile holds its 8 rows x 32 bytes), with the
+// two 16-byte chunks of a line's rows swapped in odd 8-row groups; then a
+// quarter-wave's row read (16 rows, one chunk) and a half-wave's transposing
+// read (8 rows, both chunks) each touch every bank once, and d slices, d tiles
+// and 16-row halves are immediate offsets.
 
-// the forward's LDS swizzle (conflict-free 16-byte row reads and transposing reads)
+// Copy of a tile of each tensor into LDS by waves 0 .. kCopyWaves-1: 1 KB copies
+// of 16 bytes per lane, lane l at 16 l.  Block (G, H) = the lines of d tiles 4 H ..
+// 4 H + 3 of 8-row group G: lane l carries row 8 G + (l % 16) / 2, chunk 8 H +
+// 2 (l / 16) + (l % 2 ^ G % 2).  Rows past `last` re-read it.
+template <int D, int kRows>
+__device__ __attribute__((always_inline)) inline void copy_tiles(char* dst, uint64_t a, uint64_t b,
+                                                                 uint32_t row_bytes, int last,
+                                                                 int wave, int lane) {
+  using C = Tile<D, kRows>;
+  constexpr uint32_t kSpan = 1024u * (C::N - 1);
+  int ln = lane;   // (keeps the per-lane offsets out of loop-invariant registers)
+  asm volatile("" : "+v"(ln));
+  uint32_t off[C::N];
+#pragma unroll
+  for (int i = 0; i < C::N; ++i) {
+    const int blk = wave * C::N + i;
+    const int G = blk / C::VGB;
+    const int r = 8 * G + ((ln & 15) >> 1);
+    const int ch = 8 * (blk % C::VGB) + 2 * (ln >> 4) + ((ln ^ G) & 1);
+    off[i] = uint32_t(min(r, last)) * row_bytes + (16u * ch + kSpan - 1024u * i);
+  }
+  const uint32_t d = uint32_t(size_t(LDS_PTR(char, dst))) + wave * C::N * 1024;
+  lds_copy_blocks<C::N>(d, reinterpret_cast<const char*>(a - kSpan), off);
+  lds_copy_blocks<C::N>(d + C::TILE, reinterpret_cast<const char*>(b - kSpan), off);
+}
+
+// 4 bytes per lane from src (a lane's own address) into LDS at dst + 4 lane
+__device__ inline void lds_copy_dwords(uint32_t dst, uint64_t src) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
+               :: "s"(dst), "v"(src) : "memory");
+}
+
+// Lane offsets of the two reads of a tile, and the products fed by them.
 template <int D>
-__device__ inline int swz(int r) {
-  if constexpr (D == 128) return ((r & 3) << 2) | ((r >> 2) & 3);
-  else return (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
-}
-
-__device__ inline uint32_t pack_bf16(float a, float b) {
-  f32x2 f = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
-}
-
-__device__ inline uint64_t readlane_u64(uint64_t v, int lane) {
-  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v)), lane));
-  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v >> 32)), lane));
-  return (uint64_t(hi) << 32) | uint64_t(lo);
-}
-
-// Streams the tiles of up to kMaxRuns runs of rows through an LDS ring of
-// two to four slots.  Run i (held by lane i, read with v_readlane): `len` rows of two
-// token-major tensors (row r at a + r * row_bytes and b + r * row_bytes, this
-// head's columns) and, with kVec, two float vectors (element r at
-// va + r * vec_bytes and vb + r * vec_bytes).
-template <int D, bool kVec, int kCopyWaves, int BT = kBT>
-struct Stream {
-  using C = Cfg<D, BT>;
-  static constexpr int BPW = C::BLOCKS / kCopyWaves;   // 1 KB blocks per copying wave and tensor
-  int len = 0;
-  uint64_t a = 0, b = 0, va = 0, vb = 0;
-  uint32_t row_bytes, vec_bytes;
-  int n_runs, n_tiles;
-  int sg = 0, k0 = 0;    // tile being copied next
-  int cp_row[BPW], cp_choff[BPW];
-  int wave, lane;
-
-  __device__ void init_copy_lanes() {
-#pragma unroll
-    for (int i = 0; i < BPW; ++i) {
-      const int r = (wave * BPW + i) * C::RPB + lane / C::CPR;
-      cp_row[i] = r;
-      cp_choff[i] = 16 * ((lane % C::CPR) ^ swz<D>(r));
-    }
+struct TileLanes {
+  using C = Tile<D, kBT>;
+  int row, col;
+  __device__ TileLanes(int l16, int grp) {
+    // rows: lane (l16, grp) reads row 16 h + l16, chunk 4 s + grp at row + 512 s + 16 ROWB h
+    row = (l16 >> 3) * (8 * C::ROWB) + 256 * (grp >> 1) + 32 * (l16 & 7) + 16 * ((grp ^ (l16 >> 3)) & 1);
+    // transposed: rows 4 grp .. +3 and 16 + those, d tile dt at col + 256 dt (+ 16 ROWB)
+    const int r = 4 * grp + (l16 >> 2);
+    col = (r >> 3) * (8 * C::ROWB) + 32 * (r & 7) + 16 * (((l16 >> 1) ^ (r >> 3)) & 1) + 8 * (l16 & 1);
   }
-
-  __device__ int run_len(int i) const { return __builtin_amdgcn_readlane(len, i); }
-  __device__ void advance(int& s, int& k) const {
-    k += BT;
-    if (k >= run_len(s)) {
-      ++s;
-      k = 0;
-    }
+  // rows of block kb, d slice s
+  __device__ __attribute__((always_inline)) void read_slice(const char* t, int kb, int s, bf16x8 (&x)[2]) const {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      x[h] = *reinterpret_cast<const bf16x8*>(t + (2 * kb + h) * 16 * C::ROWB + row + 512 * s);
   }
-  // copy the next tile into `slot` (rows past a partial tile's end repeat its
-  // last row); called by waves 0 .. kCopyWaves-1
-  __device__ void issue(char* slot) {
-    const int n = run_len(sg);
-    const char* ga = reinterpret_cast<const char*>(readlane_u64(a, sg));
-    const char* gb = reinterpret_cast<const char*>(readlane_u64(b, sg));
-    const bool partial = k0 + BT > n;
+  __device__ __attribute__((always_inline)) void read_rows(const char* t, int kb, bf16x8 (&x)[C::KS][2]) const {
 #pragma unroll
-    for (int i = 0; i < BPW; ++i) {
-      int tok = k0 + cp_row[i];
-      if (partial) tok = min(tok, n - 1);
-      const uint32_t off = uint32_t(tok) * row_bytes + uint32_t(cp_choff[i]);
-      char* dst = slot + (wave * BPW + i) * 1024;
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(ga + off), LDS_PTR(void, dst), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(gb + off), LDS_PTR(void, dst + C::TILE), 16, 0, 0);
-    }
-    if constexpr (kVec) {
-      if (wave == 0 && lane < BT) {   // one float per row: lanes 0 .. BT-1
-        const char* pa = reinterpret_cast<const char*>(readlane_u64(va, sg));
-        const char* pb = reinterpret_cast<const char*>(readlane_u64(vb, sg));
-        const uint32_t off = uint32_t(min(k0 + lane, n - 1)) * vec_bytes;
-        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(pa + off), LDS_PTR(void, slot + 2 * C::TILE), 4, 0, 0);
-        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(pb + off), LDS_PTR(void, slot + 2 * C::TILE + C::VEC), 4, 0, 0);
-      }
-    }
-    advance(sg, k0);
+    for (int s = 0; s < C::KS; ++s) read_slice(t, kb, s, x[s]);
   }
-};
-
-// Drives the tile loop of one workgroup over n > 0 tiles of kBlocks 32-row
-// blocks with the Ring<NS> schedule.  issue(slot) copies the stream's next
-// tile into slot (copy waves only); next_nv() returns the valid rows of the
-// next tile this wave works on and advances its cursor; block(slot, kb, nv)
-// works on block kb of the tile in slot.  With one block per tile, waves 4-7
-// work on tile t-1 while waves 0-3 work on tile t.  Slots are distinct __shared__ arrays, referenced
-// statically (the loops are unrolled by NS), so the compiler never orders a
-// read of one slot behind a copy into another.
-template <int NS, int kBlocks, int kPerTile, class Issue, class NextNv, class Block>
-__device__ __attribute__((always_inline)) inline void run_ring(int n, int wave, char* s0, char* s1,
-                                                               char* s2, char* s3, Issue& issue,
-                                                               NextNv& next_nv, Block& block) {
-  using R = Ring<NS>;
-  auto sync = [&]() __attribute__((always_inline)) {
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-  };
-  // Barrier of a copying wave before step t when tiles are copied two ahead:
-  // tile t must have landed, but tile t + 1 (issued after it, at least
-  // kPerTile memory instructions) may stay in flight if it was issued at all
-  // (t + 1 < n).  A bare s_barrier, since the workgroup fence of
-  // __syncthreads would wait for every copy.
-  static_assert(R::kAhead <= 2, "at most one tile in flight past the one read next");
-  constexpr int kKeep = (R::kAhead - 1) * kPerTile;
-  static_assert(kKeep < 16, "vmcnt field");
-  auto copy_sync = [&](int t) __attribute__((always_inline)) {
-    if constexpr (kKeep == 0) {
-      sync();
-    } else {
-      // vmcnt = kKeep or 0, lgkmcnt = 0, expcnt not waited for
-      if (t + 1 < n)
-        __builtin_amdgcn_s_waitcnt(kKeep | (7 << 4));
-      else
-        __builtin_amdgcn_s_waitcnt(7 << 4);
-      asm volatile("s_barrier" ::: "memory");
-    }
-  };
-  if constexpr (!R::kOffset) {
-    issue(s0);
-    auto step = [&](int t, char* cur, char* nxt) __attribute__((always_inline)) {
-      sync();
-      if (t + 1 < n) issue(nxt);
-      const int nv = next_nv();
-      block(cur, 0, nv);
-      if constexpr (kBlocks == 2) block(cur, 1, nv);
-    };
-    for (int t = 0; t < n;) {
-      step(t, s0, s1);
-      if (++t >= n) break;
-      step(t, s1, s0);
-      ++t;
-    }
-  } else if (wave < R::kCopyWaves) {
-    issue(s0);
-    if (R::kAhead > 1 && n > 1) issue(s1);
-    // With two tiles ahead the copies go out after the step's blocks (what the
-    // blocks reload from scratch then waits only for older copies); with one,
-    // before them (the copy needs the whole step to land).
-    auto step = [&](int t, char* cur, char* ahead) __attribute__((always_inline)) {
-      copy_sync(t);
-      if constexpr (R::kAhead < 2)
-        if (t + R::kAhead < n) issue(ahead);
-      const int nv = next_nv();
-      block(cur, 0, nv);
-      if constexpr (kBlocks == 2) block(cur, 1, nv);
-      if constexpr (R::kAhead >= 2)
-        if (t + R::kAhead < n) issue(ahead);
-    };
-    for (int t = 0; t < n;) {
-      if constexpr (NS == 3) {
-        step(t, s0, s1);
-        if (++t >= n) break;
-        step(t, s1, s2);
-        if (++t >= n) break;
-        step(t, s2, s0);
-        ++t;
-      } else {
-        step(t, s0, s2);
-        if (++t >= n) break;
-        step(t, s1, s3);
-        if (++t >= n) break;
-        step(t, s2, s0);
-        if (++t >= n) break;
-        step(t, s3, s1);
-        ++t;
-      }
-    }
-    sync();   // matches the extra barrier of waves 4-7
-  } else if constexpr (kBlocks == 1) {
-    sync();
-    // step t: barrier t, tile t-1
-    auto step = [&](int t, char* prev) __attribute__((always_inline)) {
-      sync();
-      block(prev, 0, next_nv());
-    };
-    for (int t = 1;;) {
-      if constexpr (NS == 3) {
-        step(t, s0);
-        if (t++ >= n) break;
-        step(t, s1);
-        if (t++ >= n) break;
-        step(t, s2);
-        if (t++ >= n) break;
-      } else {
-        step(t, s0);
-        if (t++ >= n) break;
-        step(t, s1);
-        if (t++ >= n) break;
-        step(t, s2);
-        if (t++ >= n) break;
-        step(t, s3);
-        if (t++ >= n) break;
-      }
-    }
-  } else {
-    sync();
-    int nv_prev = next_nv();
-    block(s0, 0, nv_prev);
-    // step t: barrier t, block 1 of tile t-1, block 0 of tile t while t < n
-    auto step = [&](int t, char* prev, char* cur) __attribute__((always_inline)) {
-      sync();
-      block(prev, 1, nv_prev);
-      if (t < n) {
-        nv_prev = next_nv();
-        block(cur, 0, nv_prev);
-      }
-    };
-    for (int t = 1;;) {
-      if constexpr (NS == 3) {
-        step(t, s0, s1);
-        if (t++ >= n) break;
-        step(t, s1, s2);
-        if (t++ >= n) break;
-        step(t, s2, s0);
-        if (t++ >= n) break;
-      } else {
-        step(t, s0, s1);
-        if (t++ >= n) break;
-        step(t, s1, s2);
-        if (t++ >= n) break;
-        step(t, s2, s3);
-        if (t++ >= n) break;
-        step(t, s3, s0);
-        if (t++ >= n) break;
-      }
-    }
-  }
-}
-
-// acc[kb] = A(rows kb*32 .. +31 of the tile) x B^T, B the stationary operand
-// (lane (l32, half) holds column l32, elements 16 ks + 8 half .. +7)
-// (kInit: added to the accumulator's initial value; kPattern: with its own
-// read-ahead schedule)
-template <int D, bool kInit = false, bool kPattern = true>
-__device__ inline void rows_times_b(const char* tile, int kb, int a_lane, const bf16x8 (&breg)[D / 16],
-                                    f32x16& acc) {
-  if constexpr (!kInit)
+  __device__ __attribute__((always_inline)) void read_cols(const char* t, int kb, bf16x8 (&x)[C::DT], int d0 = 0, int d1 = C::DT) const {
 #pragma unroll
-    for (int j = 0; j < 16; ++j) acc[j] = 0.0f;
-  const char* base = tile + kb * 32 * Cfg<D>::ROWB;
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) {
-    const bf16x8 a = *reinterpret_cast<const bf16x8*>(base + (a_lane ^ (ks << 5)));
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, breg[ks], acc, 0, 0, 0);
-  }
-  if constexpr (kPattern) {
-    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-      if (ks + 2 < D / 16) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    }
-  }
-}
-
-// out[db] += (rows kb*32 .. +31 of the tile)^T x P, P packed bf16 from the
-// accumulator layout (register j of the block = row 8 (j/4) + 4 half + j%4)
-template <int D>
-__device__ inline void rows_t_times_p(const char* tile, int kb, const int (&t_lane)[2],
-                                      const uint32_t (&pk)[8], f32x16 (&out)[D / 32]) {
-#pragma unroll
-  for (int mh = 0; mh < 2; ++mh) {
-    const u32x4 pu = {pk[4 * mh + 0], pk[4 * mh + 1], pk[4 * mh + 2], pk[4 * mh + 3]};
-    const bf16x8 pb = __builtin_bit_cast(bf16x8, pu);
-    const char* base = tile + (kb * 32 + 16 * mh) * Cfg<D>::ROWB;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) {
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, base + (t_lane[0] ^ (db << 6))));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, base + (t_lane[1] ^ (db << 6))));
+    for (int dt = d0; dt < d1; ++dt) {
+      const char* p = t + kb * 32 * C::ROWB + col + 256 * dt;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, p));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, p + 16 * C::ROWB));
       const u32x2 lo2 = __builtin_bit_cast(u32x2, lo), hi2 = __builtin_bit_cast(u32x2, hi);
-      const u32x4 au = {lo2[0], lo2[1], hi2[0], hi2[1]};
-      out[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, au), pb, out[db], 0, 0, 0);
+      const u32x4 u = {lo2[0], lo2[1], hi2[0], hi2[1]};
+      x[dt] = __builtin_bit_cast(bf16x8, u);
     }
   }
-}
-
-// lane address bases of the two LDS read patterns (as in the forward)
-template <int D>
-struct Lanes {
-  int a_lane;
-  int t_lane[2];
-  __device__ Lanes(int lane) {
-    const int l32 = lane & 31, half = lane >> 5;
-    a_lane = l32 * Cfg<D>::ROWB + ((half ^ swz<D>(l32)) << 4);
-    const int g = lane >> 4, lp = lane & 15;
-    const int v_row = 4 * (g >> 1) + (lp >> 2);
-    const int v_dsub = 16 * (g & 1) + 4 * (lp & 3);
+  // acc[dt][t] += x^T p (p packed bf16: a lane's rows 4 grp .. +3 of both halves)
+  template <int T>
+  __device__ __attribute__((always_inline)) void product(const bf16x8 (&x)[C::DT], const uint32_t (&p)[T][4],
+                                                         f32x4 (&acc)[C::DT][T]) const {
 #pragma unroll
-    for (int hi = 0; hi < 2; ++hi) {
-      const int r = v_row + 8 * hi;
-      t_lane[hi] = r * Cfg<D>::ROWB + (((v_dsub >> 3) ^ swz<D>(r)) << 4) + (v_dsub & 7) * 2;
-    }
+    for (int dt = 0; dt < C::DT; ++dt)
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const u32x4 u = {p[t][0], p[t][1], p[t][2], p[t][3]};
+        acc[dt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[dt], __builtin_bit_cast(bf16x8, u),
+                                                             acc[dt][t], 0, 0, 0);
+      }
   }
 };
 
-// load the stationary B operand of one wave: 32 columns (rows of a token-major
-// tensor, clamped to n - 1), lane (l32, half) gets elements 16 ks + 8 half .. +7
-template <int D>
-__device__ inline void load_b(const __bf16* base, int64_t row_elems, int col0, int n, int lane,
-                              bf16x8 (&breg)[D / 16]) {
-  const int r = min(col0 + (lane & 31), n - 1);
-  const __bf16* p = base + int64_t(r) * row_elems + 8 * (lane >> 5);
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) breg[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
-}
+// Cursor over the tiles of the runs: tile = (run, first row).
+struct Cursor {
+  int sg, k0;
+};
 
-// Stationary operand kept in LDS instead of registers (register budget): the
-// 32 rows of wave w at stat + (32 w + r) * ROWB, 16-byte chunks swizzled as in
-// the tiles, so reading it back as a B operand is conflict-free.
-template <int D>
-__device__ inline void stash_b(char* stat, const __bf16* base, int64_t row_elems, int col0, int n,
-                               int wave, int lane) {
-  // lane l writes chunks l % CPR (and l % CPR + ..) of rows: 64 lanes cover 64 * 16 B per pass
-  constexpr int CPR = Cfg<D>::CPR;
-#pragma unroll
-  for (int pass = 0; pass < 32 * CPR / 64; ++pass) {
-    const int idx = pass * 64 + lane;
-    const int r = idx / CPR, ch = idx % CPR;
-    const int src = min(col0 + r, n - 1);
-    const u32x4 v = *reinterpret_cast<const u32x4*>(base + int64_t(src) * row_elems + 8 * ch);
-    *reinterpret_cast<u32x4*>(stat + (32 * wave + r) * Cfg<D>::ROWB + ((ch ^ swz<D>(r)) << 4)) = v;
-  }
+// NM products, each followed by its share of NR LDS reads, NV plain VALU and NT
+// transcendentals (sched_group_barrier classes 0x008, 0x100, 0x002, 0x400), after
+// NRF reads ahead of the first one
+template <int NM, int NR, int NRF, int NV, int NT, int... I>
+__device__ __forceinline__ void interleave_seq(std::integer_sequence<int, I...>) {
+  auto one = [](auto ic) __attribute__((always_inline)) {
+    constexpr int i = decltype(ic)::value;
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    constexpr int r = ((NR - NRF) * (i + 1)) / NM - ((NR - NRF) * i) / NM;
+    if constexpr (r > 0) __builtin_amdgcn_sched_group_barrier(0x100, r, 0);
+    constexpr int v = (NV * (i + 1)) / NM - (NV * i) / NM;
+    if constexpr (v > 0) __builtin_amdgcn_sched_group_barrier(0x002, v, 0);
+    constexpr int t = (NT * (i + 1)) / NM - (NT * i) / NM;
+    if constexpr (t > 0) __builtin_amdgcn_sched_group_barrier(0x400, t, 0);
+  };
+  (one(std::integral_constant<int, I>{}), ...);
 }
-
-// acc = A(rows kb*32 .. +31 of the tile) x B^T with B read from the stash
-// (kPattern: with its own read-ahead schedule)
-template <int D, bool kPattern = true>
-__device__ inline void rows_times_stash(const char* tile, int kb, int a_lane, const char* stat_w,
-                                        f32x16& acc) {
-#pragma unroll
-  for (int j = 0; j < 16; ++j) acc[j] = 0.0f;
-  const char* base = tile + kb * 32 * Cfg<D>::ROWB;
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) {
-    const bf16x8 a = *reinterpret_cast<const bf16x8*>(base + (a_lane ^ (ks << 5)));
-    const bf16x8 b = *reinterpret_cast<const bf16x8*>(stat_w + (a_lane ^ (ks << 5)));
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-  }
-  if constexpr (kPattern) {
-    // operands read two products ahead at most (register budget)
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-      if (ks + 2 < D / 16) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    }
-  }
-}
-
-// store scale * acc^T: acc rows = d (32 db + 8 (j/4) + 4 half + j%4), columns = lanes
-template <int D>
-__device__ inline void store_t(__bf16* base, int64_t row_elems, int col, int n, int lane,
-                               const f32x16 (&acc)[D / 32], float scale) {
-  if (col >= n) return;
-  __bf16* p = base + int64_t(col) * row_elems + 4 * (lane >> 5);
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      u32x2 w;
-      w.x = pack_bf16(acc[db][4 * a + 0] * scale, acc[db][4 * a + 1] * scale);
-      w.y = pack_bf16(acc[db][4 * a + 2] * scale, acc[db][4 * a + 3] * scale);
-      *reinterpret_cast<u32x2*>(p + 32 * db + 8 * a) = w;
-    }
+template <int NM, int NR, int NRF, int NV, int NT>
+__device__ __forceinline__ void interleave() {
+  if constexpr (NRF > 0) __builtin_amdgcn_sched_group_barrier(0x100, NRF, 0);
+  interleave_seq<NM, NR, NRF, NV, NT>(std::make_integer_sequence<int, NM>{});
 }
 
 __device__ inline int xcd_logical(int b, int n_wg) {
@@ -493,321 +221,558 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(const __bf16* __restrict
 }
 
 // ---- dQ: query-stationary ---------------------------------------------------------------
-// Slot = K tile then V tile (the queries' log-sum-exp and D sit in lanes).
-template <int D, int NS>
-__device__ __attribute__((always_inline)) inline void dq_body(
-    const __bf16* __restrict__ q, const __bf16* __restrict__ dout, const float* __restrict__ lse,
-    const float* __restrict__ delta, __bf16* __restrict__ dq, int heads, float c_log2, float scale,
-    const PackedPlan& plan, int n_qtiles, char* s0, char* s1, char* s2, char* s3, char* stash) {
-  using C = Cfg<D>;
-  using R = Ring<NS>;
-  const int nq = plan.chunk_tokens;
-  const int logical = xcd_interleaved(blockIdx.x, gridDim.x, n_qtiles);
-  const int chunk = logical / (heads * n_qtiles);
-  const int rest = logical - chunk * heads * n_qtiles;
-  const int head = rest / n_qtiles, qt = rest % n_qtiles;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
-  const int64_t tok0 = int64_t(chunk) * nq;
-  const int64_t row_elems = int64_t(heads) * D;
-  const int q0 = qt * kBlockN + wave * 32;
-
-  bf16x8 qreg[C::KS];
-  load_b<D>(q + tok0 * row_elems + head * D, row_elems, q0, nq, lane, qreg);
-  stash_b<D>(stash, dout + tok0 * row_elems + head * D, row_elems, q0, nq, wave, lane);
-  const char* stash_w = stash + 32 * wave * C::ROWB;
-  const int qi = min(q0 + l32, nq - 1);
-  const float L = lse[(tok0 + qi) * heads + head];
-  const float Dq = delta[(tok0 + qi) * heads + head];
-  f32x16 acc[C::DB];
-#pragma unroll
-  for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-    for (int j = 0; j < 16; ++j) acc[db][j] = 0.0f;
-
-  Stream<D, false, R::kCopyWaves> st;
-  st.wave = wave;
-  st.lane = lane;
-  st.row_bytes = uint32_t(2 * row_elems);
-  st.n_runs = packed_num_segments(plan, chunk);
-#pragma unroll
-  for (int i = 0; i < kMaxRuns; ++i)
-    if (lane == i && i < st.n_runs) {
-      const KvSegment sg = packed_segment(plan, chunk, i, heads, D, 2);
-      st.len = sg.len;
-      st.a = reinterpret_cast<uint64_t>(sg.k) + 2ull * uint64_t(head) * D;
-      st.b = reinterpret_cast<uint64_t>(sg.v) + 2ull * uint64_t(head) * D;
-    }
-  st.n_tiles = 0;
-  for (int i = 0; i < st.n_runs; ++i) st.n_tiles += (st.run_len(i) + kBT - 1) / kBT;
-  st.init_copy_lanes();
-  Lanes<D> ln(lane);
-  int csg = 0, ck0 = 0;   // next tile this wave works on
-
-  auto issue = [&](char* slot) __attribute__((always_inline)) { st.issue(slot); };
-  auto next_nv = [&]() __attribute__((always_inline)) {
-    const int nv = min(kBT, st.run_len(csg) - ck0);
-    st.advance(csg, ck0);
-    return nv;
-  };
-  auto block = [&](const char* cur, int kb, int nv) __attribute__((always_inline)) {
-    // keep the per-read address arithmetic inside the loop (no hoisted copies)
-    asm volatile("" : "+v"(ln.a_lane), "+v"(ln.t_lane[0]), "+v"(ln.t_lane[1]));
-    f32x16 sv, dp;
-    rows_times_b<D>(cur, kb, ln.a_lane, qreg, sv);                      // S^T = K Q^T
-    __builtin_amdgcn_sched_barrier(0);
-    rows_times_stash<D>(cur + C::TILE, kb, ln.a_lane, stash_w, dp);     // dP^T = V dO^T
-    __builtin_amdgcn_sched_barrier(0);
-    uint32_t pk[8];
-#pragma unroll
-    for (int j = 0; j < 16; j += 2) {
-      float v2[2];
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const int key = kb * 32 + 8 * ((j + e) >> 2) + 4 * half + ((j + e) & 3);
-        const float p = key < nv ? __builtin_amdgcn_exp2f(fmaf(sv[j + e], c_log2, -L)) : 0.0f;
-        v2[e] = p * (dp[j + e] - Dq);
-      }
-      pk[j >> 1] = pack_bf16(v2[0], v2[1]);
-    }
-    rows_t_times_p<D>(cur, kb, ln.t_lane, pk, acc);                     // dQ^T += K^T dS^T
-    __builtin_amdgcn_sched_barrier(0);   // one 32-key block at a time (register budget)
-  };
-  if (st.n_tiles > 0)
-    run_ring<NS, 2, 2 * decltype(st)::BPW>(st.n_tiles, wave, s0, s1, s2, s3, issue, next_nv, block);
-  store_t<D>(dq + tok0 * row_elems + head * D, row_elems, q0 + l32, nq, lane, acc, scale);
-}
-
-template <int D, int NS>
+// A workgroup holds 256 queries of one chunk and head (32 per wave, Q and dO in
+// registers) and streams the 64-key tiles of their read set through a ring of
+// five slots (K tile, V tile), as the forward kernel does: waves 0-3 copy three
+// tiles ahead, one barrier per tile.  Products on v_mfma_f32_16x16x32_bf16 (the
+// least register traffic per FLOP).  One step per 32-key block b, in three
+// scheduling regions of 16 products each:
+//   S^T(b) = K Q^T              with dS of block b-1 (P (dP - D), bf16 packs) between its products
+//   dP^T(b) = V dO^T            with P(b) = 2^(c S - L) between its products
+//   dQ^T += K(b-1)^T dS(b-1)^T
+// so the VALU work of a block never waits for products of its own region, and
+// each region reads the LDS operands of the next one.
+template <int D>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ dout,
                    const float* __restrict__ lse, const float* __restrict__ delta,
                    __bf16* __restrict__ dq, int heads, float c_log2, float scale, PackedPlan plan,
                    int n_qtiles) {
-  constexpr int kSlot = 2 * Cfg<D>::TILE;
-  __shared__ __attribute__((aligned(1024))) char stash[kBlockN * Cfg<D>::ROWB];
-  __shared__ __attribute__((aligned(1024))) char l0[kSlot];
-  __shared__ __attribute__((aligned(1024))) char l1[kSlot];
-  if constexpr (NS == 2) {
-    dq_body<D, NS>(q, dout, lse, delta, dq, heads, c_log2, scale, plan, n_qtiles, l0, l1, l1, l1, stash);
-  } else if constexpr (NS == 3) {
-    __shared__ __attribute__((aligned(1024))) char l2[kSlot];
-    dq_body<D, NS>(q, dout, lse, delta, dq, heads, c_log2, scale, plan, n_qtiles, l0, l1, l2, l2, stash);
-  } else {
-    __shared__ __attribute__((aligned(1024))) char l2[kSlot];
-    __shared__ __attribute__((aligned(1024))) char l3[kSlot];
-    dq_body<D, NS>(q, dout, lse, delta, dq, heads, c_log2, scale, plan, n_qtiles, l0, l1, l2, l3, stash);
+  using C = Tile<D, kBT>;
+  __shared__ __attribute__((aligned(1024))) char lds[5 * C::SLOT];
+  const int nq = plan.chunk_tokens;
+  const int logical = xcd_interleaved(blockIdx.x, gridDim.x, n_qtiles);
+  const int chunk = logical / (heads * n_qtiles);
+  const int rest = logical - chunk * heads * n_qtiles;
+  const int head = rest / n_qtiles, qt = rest % n_qtiles;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, l16 = lane & 15, grp = lane >> 4;
+  const int64_t tok0 = int64_t(chunk) * nq;
+  const int64_t row_elems = int64_t(heads) * D;
+  const int q0 = qt * kBlockN + wave * 32;
+  const bool idle = q0 >= nq;   // no queries for this wave: it only copies and keeps the barriers
+
+  // lane (l16, grp) holds query q0 + 16 qh + l16, elements 32 s + 8 grp .. +7
+  bf16x8 qreg[2][C::KS], greg[2][C::KS];
+  float L[2], Dq_[2];
+#pragma unroll
+  for (int qh = 0; qh < 2; ++qh) {
+    const int64_t t = tok0 + min(q0 + 16 * qh + l16, nq - 1);
+    const __bf16* qp = q + t * row_elems + head * D + 8 * grp;
+    const __bf16* gp = dout + t * row_elems + head * D + 8 * grp;
+#pragma unroll
+    for (int s = 0; s < C::KS; ++s) {
+      qreg[qh][s] = *reinterpret_cast<const bf16x8*>(qp + 32 * s);
+      greg[qh][s] = *reinterpret_cast<const bf16x8*>(gp + 32 * s);
+    }
+    L[qh] = lse[t * heads + head];
+    Dq_[qh] = delta[t * heads + head];
+  }
+  f32x4 acc[C::DT][2];
+#pragma unroll
+  for (int dt = 0; dt < C::DT; ++dt)
+#pragma unroll
+    for (int qh = 0; qh < 2; ++qh) acc[dt][qh] = f32x4{};
+
+  // runs of the read set, one per lane (read with v_readlane)
+  const int n_runs = packed_num_segments(plan, chunk);
+  int sg_len = 0;
+  uint64_t sg_k = 0, sg_v = 0;
+  const uint32_t row_bytes = uint32_t(2 * row_elems);
+#pragma unroll
+  for (int i = 0; i < kMaxRuns; ++i)
+    if (lane == i && i < n_runs) {
+      const KvSegment sg = packed_segment(plan, chunk, i, heads, D, 2);
+      sg_len = sg.len;
+      sg_k = reinterpret_cast<uint64_t>(sg.k) + 2ull * uint64_t(head) * D;
+      sg_v = reinterpret_cast<uint64_t>(sg.v) + 2ull * uint64_t(head) * D;
+    }
+  auto run_len = [&](int i) { return __builtin_amdgcn_readlane(sg_len, i); };
+  int n_tiles = 0;
+  for (int i = 0; i < n_runs; ++i) n_tiles += (run_len(i) + kBT - 1) / kBT;
+  auto advance = [&](Cursor c) __attribute__((always_inline)) {
+    c.k0 += kBT;
+    if (c.k0 >= run_len(c.sg)) {
+      ++c.sg;
+      c.k0 = 0;
+    }
+    return c;
+  };
+  auto slot = [&](int i) __attribute__((always_inline)) { return lds + i * C::SLOT; };
+
+  auto issue_tile = [&](char* base, Cursor c) __attribute__((always_inline)) {
+    if (wave >= C::kCopyWaves) return;
+    const uint64_t off = uint64_t(c.k0) * row_bytes;
+    copy_tiles<D, kBT>(base, readlane_u64(sg_k, c.sg) + off, readlane_u64(sg_v, c.sg) + off, row_bytes,
+                  run_len(c.sg) - 1 - c.k0, wave, lane);
+  };
+  const TileLanes<D> ln(l16, grp);
+  auto rows_product = [&](const bf16x8 (&x)[C::KS][2], const bf16x8 (&st)[2][C::KS], f32x4 (&r)[2][2])
+      __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < C::KS; ++s)
+#pragma unroll
+      for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+        for (int qh = 0; qh < 2; ++qh)
+          r[kh][qh] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[s][kh], st[qh][s],
+                                                              s == 0 ? f32x4{} : r[kh][qh], 0, 0, 0);
+  };
+
+  // p and dp: P and dP^T of the previous block
+  f32x4 p[2][2], dp[2][2];
+#pragma unroll
+  for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+    for (int qh = 0; qh < 2; ++qh) {
+      p[kh][qh] = f32x4{};
+      dp[kh][qh] = f32x4{};
+    }
+  // dS of the previous block, packed as the B operand of dQ^T
+  auto ds_pack = [&](uint32_t (&pk)[2][4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int qh = 0; qh < 2; ++qh)
+#pragma unroll
+      for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+        for (int j = 0; j < 4; j += 2)
+          pk[qh][2 * kh + (j >> 1)] = pack_bf16(p[kh][qh][j] * (dp[kh][qh][j] - Dq_[qh]),
+                                                p[kh][qh][j + 1] * (dp[kh][qh][j + 1] - Dq_[qh]));
+  };
+  // One step: block kb of the tile in st, whose K rows are in kx; (pt, pkb): the
+  // previous block's tile and index, (nt, nkb): the next one's.  Each region reads
+  // the operands of the next one.
+  auto step = [&](bf16x8 (&kx)[C::KS][2], const char* st, int kb, const char* pt, int pkb,
+                  const char* nt, int nkb, int nv) __attribute__((always_inline)) {
+    uint32_t pk[2][4];
+    f32x4 s[2][2];
+    bf16x8 vx[C::KS][2], cx[C::DT];
+    ln.read_rows(st + C::TILE, kb, vx);
+    ds_pack(pk);
+    rows_product(kx, qreg, s);
+    interleave<4 * C::KS, 2 * C::KS, 0, 44, 0>();
+    asm volatile("" ::"v"(pk[0][0]), "v"(pk[0][1]), "v"(pk[0][2]), "v"(pk[0][3]), "v"(pk[1][0]),
+                 "v"(pk[1][1]), "v"(pk[1][2]), "v"(pk[1][3]));
+    __builtin_amdgcn_sched_barrier(0);
+    ln.read_cols(pt, pkb, cx);
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+      for (int qh = 0; qh < 2; ++qh)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          p[kh][qh][j] = __builtin_amdgcn_exp2f(fmaf(s[kh][qh][j], c_log2, -L[qh]));
+    rows_product(vx, greg, dp);
+    interleave<4 * C::KS, 2 * C::DT, 0, 20, 16>();
+    __builtin_amdgcn_sched_barrier(0);
+    ln.read_rows(nt, nkb, kx);
+    ln.template product<2>(cx, pk, acc);
+    interleave<2 * C::DT, 2 * C::KS, 0, 0, 0>();
+    __builtin_amdgcn_sched_barrier(0);
+    if (nv < kBT)   // keys past a run's end
+#pragma unroll
+      for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+        for (int qh = 0; qh < 2; ++qh)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            p[kh][qh][j] = 4 * grp >= nv - 32 * kb - 16 * kh - j ? 0.0f : p[kh][qh][j];
+  };
+
+  Cursor c_t = {0, 0}, c_dma = {0, 0};
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    if (i < n_tiles) {
+      issue_tile(slot(i), c_dma);
+      c_dma = advance(c_dma);
+    }
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (idle) {   // only the copies and the barriers of the loop below
+    int i3 = 3;
+#pragma unroll 1
+    for (int t = 0; t < n_tiles; ++t) {
+      if (wave < C::kCopyWaves) {
+        if (t + 2 < n_tiles)
+          __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * C::N));
+        else
+          __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+      }
+      asm volatile("s_barrier" ::: "memory");
+      if (t + 3 < n_tiles) {
+        issue_tile(slot(i3), c_dma);
+        c_dma = advance(c_dma);
+      }
+      i3 = i3 == 4 ? 0 : i3 + 1;
+    }
+    return;
+  }
+  bf16x8 kx[C::KS][2];
+  ln.read_rows(slot(0), 0, kx);
+  // barrier t: tile t+1 has landed (each copying wave waits for its own copies)
+  // and tile t-2 is no longer read; then tile t+3 is copied into its slot
+  int i0 = 0;   // slot of tile t
+#pragma unroll 1
+  for (int t = 0; t < n_tiles; ++t) {
+    const int i1 = i0 == 4 ? 0 : i0 + 1;
+    const int i4 = i0 == 0 ? 4 : i0 - 1;        // slot of tile t-1
+    const int i3 = i0 >= 2 ? i0 - 2 : i0 + 3;   // slot of tile t-2 (and of tile t+3)
+    if (wave < C::kCopyWaves) {
+      if (t + 2 < n_tiles)
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * C::N));
+      else
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    }
+    asm volatile("s_barrier" ::: "memory");
+    if (t + 3 < n_tiles) {
+      issue_tile(slot(i3), c_dma);
+      c_dma = advance(c_dma);
+    }
+    const int nv = min(kBT, run_len(c_t.sg) - c_t.k0);
+    c_t = advance(c_t);
+    char* st = slot(i0);
+    // (the first step adds dS = 0 times tile 0's K; after the last tile the next
+    // block's K rows come from a stale slot and are not used)
+    step(kx, st, 0, t == 0 ? st : slot(i4), 1, st, 1, nv);
+    step(kx, st, 1, st, 0, slot(i1), 0, nv);
+    i0 = i1;
+  }
+  {
+    // the last block
+    uint32_t pk[2][4];
+    ds_pack(pk);
+    bf16x8 x[C::DT];
+    ln.read_cols(slot(i0 == 0 ? 4 : i0 - 1), 1, x);
+    ln.template product<2>(x, pk, acc);
+  }
+
+#pragma unroll
+  for (int qh = 0; qh < 2; ++qh) {
+    const int qi = q0 + 16 * qh + l16;
+    if (qi < nq) {
+      __bf16* op = dq + (tok0 + qi) * row_elems + head * D + 4 * grp;
+#pragma unroll
+      for (int dt = 0; dt < C::DT; ++dt) {
+        u32x2 w;
+        w.x = pack_bf16(acc[dt][qh][0] * scale, acc[dt][qh][1] * scale);
+        w.y = pack_bf16(acc[dt][qh][2] * scale, acc[dt][qh][3] * scale);
+        *reinterpret_cast<u32x2*>(op + 16 * dt) = w;
+      }
+    }
   }
 }
 
-// ---- dK or dV: key-stationary -----------------------------------------------------------
-// Key units: unit u < n_chunks * kpc is keys [256 k, 256 k + 256) of chunk
-// u / kpc; the rest are anchor frames, kpf units each.  Each unit streams the
-// query runs that see it (chunks max(0, .) .. c + window of the packed clip,
-// or the chunk runs listed for the anchor frame).
+// ---- dK and dV: key-stationary ----------------------------------------------------------
+// Key units: the first n_frames * kpf units are anchor frames, kpf units of 256 keys
+// each, the rest are keys [256 k, 256 k + 256) of a chunk, kpc units per chunk.  Each unit
+// streams the query runs that see it (the chunk runs listed for the anchor
+// frame, or chunks c .. c + window of the packed clip).  Frames come first: they
+// are seen by the most chunks, and the longest streams should not start last.
 struct KeyUnits {
   int32_t kpc, kpf, n_frames;
   uint8_t frame_runs[FF_MAX_ANCHOR_FRAMES * 8][16];   // per anchor frame: (first chunk, count) pairs
 };
 
-// dK and dV of one key unit.  Slot = Q tile, dO tile, their log-sum-exp and D.
-template <int D, int NS, int BT>
-__device__ __attribute__((always_inline)) inline void dkv_body(
-    const __bf16* __restrict__ q, const __bf16* __restrict__ dout, const float* __restrict__ lse,
-    const float* __restrict__ delta, __bf16* __restrict__ dk_chunks, __bf16* __restrict__ dk_anchor,
-    __bf16* __restrict__ dv_chunks, __bf16* __restrict__ dv_anchor, int heads, float c_log2,
-    float scale, const PackedPlan& plan, const KeyUnits& ku, char* s0, char* s1, char* s2, char* s3,
-    char* stash) {
-  using C = Cfg<D, BT>;
-  using R = Ring<NS>;
-  constexpr int kBlocks = BT / 32;
-  const int nq = plan.chunk_tokens, G = plan.frame_tokens;
-  const int n_units = plan.n_chunks * ku.kpc + ku.n_frames * ku.kpf;
-  const int logical = xcd_logical(blockIdx.x, gridDim.x);
-  const int head = logical / n_units;
-  const int unit = logical - head * n_units;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
-  const int64_t row_elems = int64_t(heads) * D;
-  const bool is_chunk = unit < plan.n_chunks * ku.kpc;
-  int owner, k_first, n_keys;
-  const __bf16 *kbase, *vbase;
-  __bf16 *obase_k, *obase_v;
-  if (is_chunk) {
-    owner = unit / ku.kpc;
-    k_first = (unit % ku.kpc) * kBlockN;
-    n_keys = nq;
-    kbase = static_cast<const __bf16*>(plan.k) + int64_t(owner) * nq * row_elems;
-    vbase = static_cast<const __bf16*>(plan.v) + int64_t(owner) * nq * row_elems;
-    obase_k = dk_chunks + int64_t(owner) * nq * row_elems;
-    obase_v = dv_chunks + int64_t(owner) * nq * row_elems;
-  } else {
-    const int a = unit - plan.n_chunks * ku.kpc;
-    owner = a / ku.kpf;
-    k_first = (a % ku.kpf) * kBlockN;
-    n_keys = G;
-    kbase = static_cast<const __bf16*>(plan.ak) + int64_t(owner) * G * row_elems;
-    vbase = static_cast<const __bf16*>(plan.av) + int64_t(owner) * G * row_elems;
-    obase_k = dk_anchor + int64_t(owner) * G * row_elems;
-    obase_v = dv_anchor + int64_t(owner) * G * row_elems;
-  }
-  const int k0 = k_first + wave * 32;
-  bf16x8 kreg[C::KS];
-  load_b<D>(kbase + head * D, row_elems, k0, n_keys, lane, kreg);
-  stash_b<D>(stash, vbase + head * D, row_elems, k0, n_keys, wave, lane);
-  const char* stash_w = stash + 32 * wave * C::ROWB;
-  f32x16 acc[C::DB], acc_v[C::DB];   // dK^T, dV^T
-#pragma unroll
-  for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      acc[db][j] = 0.0f;
-      acc_v[db][j] = 0.0f;
-    }
-
-  // query runs of this unit
-  Stream<D, true, R::kCopyWaves, BT> st;
-  st.wave = wave;
-  st.lane = lane;
-  st.row_bytes = uint32_t(2 * row_elems);
-  st.vec_bytes = uint32_t(4 * heads);
-  auto set_run = [&](int i, int c0, int c1) {   // chunks c0 .. c1 - 1
-    if (lane == i) {
-      const int64_t t0 = int64_t(c0) * nq;
-      st.len = (c1 - c0) * nq;
-      st.a = reinterpret_cast<uint64_t>(q + t0 * row_elems + head * D);
-      st.b = reinterpret_cast<uint64_t>(dout + t0 * row_elems + head * D);
-      st.va = reinterpret_cast<uint64_t>(lse + t0 * heads + head);
-      st.vb = reinterpret_cast<uint64_t>(delta + t0 * heads + head);
-    }
-  };
-  if (is_chunk) {
-    set_run(0, owner, min(owner + plan.window + 1, plan.n_chunks));
-    st.n_runs = 1;
-  } else {
-    int n = 0;
-    while (n < 8 && ku.frame_runs[owner][2 * n + 1] != 0) {
-      const int c0 = ku.frame_runs[owner][2 * n];
-      set_run(n, c0, c0 + ku.frame_runs[owner][2 * n + 1]);
-      ++n;
-    }
-    st.n_runs = n;
-  }
-  st.n_tiles = 0;
-  for (int i = 0; i < st.n_runs; ++i) st.n_tiles += (st.run_len(i) + BT - 1) / BT;
-  st.init_copy_lanes();
-  Lanes<D> ln(lane);
-  int csg = 0, ck0 = 0;   // next tile this wave works on
-
-  auto issue = [&](char* slot) __attribute__((always_inline)) { st.issue(slot); };
-  auto next_nv = [&]() __attribute__((always_inline)) {
-    const int nv = min(BT, st.run_len(csg) - ck0);
-    st.advance(csg, ck0);
-    return nv;
-  };
-  // One 32-query block in four scheduling regions: (1) S - L / c (L / c as the
-  // accumulator's initial value); (2) dP, with P = 2^(c (S - L / c)) computed
-  // under its products; (3) dV^T += dO^T P, with dS = P (dP - D) computed and
-  // packed under its products; (4) dK^T += Q^T dS.
-  const float neg_inv_c = -1.0f / c_log2;
-  auto block = [&](const char* cur, int kb, int nv) __attribute__((always_inline)) {
-    // keep the per-read address arithmetic inside the loop (no hoisted copies)
-    asm volatile("" : "+v"(ln.a_lane), "+v"(ln.t_lane[0]), "+v"(ln.t_lane[1]));
-    const float* lse_t = reinterpret_cast<const float*>(cur + 2 * C::TILE);
-    const float* del_t = reinterpret_cast<const float*>(cur + 2 * C::TILE + C::VEC);
-    const int row0 = kb * 32 + 4 * half;   // register 4 g + e: row row0 + 8 g + e
-    f32x16 sv;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const f32x4 Lr = *reinterpret_cast<const f32x4*>(lse_t + row0 + 8 * g);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sv[4 * g + e] = Lr[e] * neg_inv_c;
-    }
-    rows_times_b<D, true, false>(cur, kb, ln.a_lane, kreg, sv);   // S - L / c (rows = queries)
-    __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);   // L and the first two operands
-    __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
-#pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) {
-      if (ks + 2 < C::KS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    f32x16 dp;
-    rows_times_stash<D, false>(cur + C::TILE, kb, ln.a_lane, stash_w, dp);   // dP = dO V^T
-    float p[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) p[j] = __builtin_amdgcn_exp2f(sv[j] * c_log2);
-    // the first two products' operands; then per product two reads, two
-    // multiplies and two exponentials
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (ks + 2 < C::KS) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (nv < BT) {   // rows past a partial tile's end
-#pragma unroll
-      for (int j = 0; j < 16; ++j)
-        if (row0 + 8 * (j >> 2) + (j & 3) >= nv) p[j] = 0.0f;
-    }
-    uint32_t pk[8], pv[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) pv[i] = pack_bf16(p[2 * i], p[2 * i + 1]);
-    rows_t_times_p<D>(cur + C::TILE, kb, ln.t_lane, pv, acc_v);   // dV^T += dO^T P
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const f32x4 Dr = *reinterpret_cast<const f32x4*>(del_t + row0 + 8 * g);
-      float ds[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) ds[e] = p[4 * g + e] * (dp[4 * g + e] - Dr[e]);
-      pk[2 * g] = pack_bf16(ds[0], ds[1]);
-      pk[2 * g + 1] = pack_bf16(ds[2], ds[3]);
-    }
-    // D and the first two products' operands, the packs they need; then per
-    // product two reads and five VALU (the other packs, dS)
-    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-#pragma unroll
-    for (int i = 0; i < 2 * C::DB; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (i + 2 < 2 * C::DB) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    rows_t_times_p<D>(cur, kb, ln.t_lane, pk, acc);              // dK^T += Q^T dS
-    __builtin_amdgcn_sched_barrier(0);   // one 32-query block at a time (register budget)
-  };
-  if (st.n_tiles > 0)
-    run_ring<NS, kBlocks, 2 * decltype(st)::BPW>(st.n_tiles, wave, s0, s1, s2, s3, issue, next_nv,
-                                                 block);
-  store_t<D>(obase_k + head * D, row_elems, k0 + l32, n_keys, lane, acc, scale);
-  store_t<D>(obase_v + head * D, row_elems, k0 + l32, n_keys, lane, acc_v, 1.0f);
-}
-
-template <int D, int NS, int BT>
+// A workgroup holds 256 keys (32 per wave: K in registers, V in LDS, where the
+// registers run out beside both accumulators) and streams tiles of 32 queries (64
+// at d = 64, where a tile of 32 is worked on for less time than a copy takes; Q, dO,
+// the log-sum-exp and D) through a ring of five slots, with one barrier per two
+// tiles: at the barrier of tiles t and t+1, tile t+2 has landed too (its Q rows are
+// read ahead) and tiles t+3 and t+4 go into the slots of t-2 and t-1.  A block of 32
+// queries in four scheduling regions of 16 products, each reading ahead what the registers
+// allow of the next one's LDS operands:
+//   S = Q K^T - L / c    (L / c enters as the accumulator's initial value)
+//   dP = dO V^T          with P = 2^(c S) between its products
+//   dV^T += dO^T P       with dS = P (dP - D) and the bf16 packs between its products
+//   dK^T += Q^T dS
+template <int D>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ dout,
                     const float* __restrict__ lse, const float* __restrict__ delta,
                     __bf16* __restrict__ dk_chunks, __bf16* __restrict__ dk_anchor,
                     __bf16* __restrict__ dv_chunks, __bf16* __restrict__ dv_anchor, int heads,
                     float c_log2, float scale, PackedPlan plan, KeyUnits ku) {
-  constexpr int kSlot = 2 * Cfg<D, BT>::TILE + 2 * Cfg<D, BT>::VEC;
-  __shared__ __attribute__((aligned(1024))) char stash[kBlockN * Cfg<D>::ROWB];
-  __shared__ __attribute__((aligned(1024))) char l0[kSlot];
-  __shared__ __attribute__((aligned(1024))) char l1[kSlot];
-  if constexpr (NS == 2) {
-    dkv_body<D, NS, BT>(q, dout, lse, delta, dk_chunks, dk_anchor, dv_chunks, dv_anchor, heads,
-                           c_log2, scale, plan, ku, l0, l1, l1, l1, stash);
-  } else if constexpr (NS == 3) {
-    __shared__ __attribute__((aligned(1024))) char l2[kSlot];
-    dkv_body<D, NS, BT>(q, dout, lse, delta, dk_chunks, dk_anchor, dv_chunks, dv_anchor, heads,
-                           c_log2, scale, plan, ku, l0, l1, l2, l2, stash);
+  constexpr int kRows = D == 128 ? 32 : 64;        // queries per tile
+  constexpr int kBlocks = kRows / 32;
+  using C = Tile<D, kRows>;
+  constexpr int kSlot = C::SLOT + 2 * kRows * 4;   // Q tile, dO tile, L, D
+  __shared__ __attribute__((aligned(1024))) char stash[kBlockN * C::ROWB];
+  __shared__ __attribute__((aligned(1024))) char lds[5 * kSlot];
+  const int nq = plan.chunk_tokens, G = plan.frame_tokens;
+  const int n_frame_units = ku.n_frames * ku.kpf;
+  const int n_units = n_frame_units + plan.n_chunks * ku.kpc;
+  const int logical = xcd_logical(blockIdx.x, gridDim.x);
+  const int head = logical / n_units;
+  const int unit = logical - head * n_units;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, l16 = lane & 15, grp = lane >> 4;
+  const int64_t row_elems = int64_t(heads) * D;
+  const bool is_chunk = unit >= n_frame_units;
+  int owner, k_first, n_keys;
+  const __bf16 *kbase, *vbase;
+  __bf16 *obase_k, *obase_v;
+  if (is_chunk) {
+    const int u = unit - n_frame_units;
+    owner = u / ku.kpc;
+    k_first = (u % ku.kpc) * kBlockN;
+    n_keys = nq;
+    const int64_t o = int64_t(owner) * nq * row_elems + head * D;
+    kbase = static_cast<const __bf16*>(plan.k) + o;
+    vbase = static_cast<const __bf16*>(plan.v) + o;
+    obase_k = dk_chunks + o;
+    obase_v = dv_chunks + o;
   } else {
-    __shared__ __attribute__((aligned(1024))) char l2[kSlot];
-    __shared__ __attribute__((aligned(1024))) char l3[kSlot];
-    dkv_body<D, NS, BT>(q, dout, lse, delta, dk_chunks, dk_anchor, dv_chunks, dv_anchor, heads,
-                           c_log2, scale, plan, ku, l0, l1, l2, l3, stash);
+    owner = unit / ku.kpf;
+    k_first = (unit % ku.kpf) * kBlockN;
+    n_keys = G;
+    const int64_t o = int64_t(owner) * G * row_elems + head * D;
+    kbase = static_cast<const __bf16*>(plan.ak) + o;
+    vbase = static_cast<const __bf16*>(plan.av) + o;
+    obase_k = dk_anchor + o;
+    obase_v = dv_anchor + o;
+  }
+  const int k0 = k_first + wave * 32;
+  const bool idle = k0 >= n_keys;   // no keys for this wave: it only copies and keeps the barriers
+
+  // lane (l16, grp) holds key k0 + 16 t + l16, elements 32 s + 8 grp .. +7
+  bf16x8 kreg[2][C::KS];
+  char* stash_w = stash + 32 * wave * C::ROWB;
+  const TileLanes<D> ln(l16, grp);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int64_t r = min(k0 + 16 * t + l16, n_keys - 1);
+    const __bf16* kp = kbase + r * row_elems + 8 * grp;
+    const __bf16* vp = vbase + r * row_elems + 8 * grp;
+#pragma unroll
+    for (int s = 0; s < C::KS; ++s) {
+      kreg[t][s] = *reinterpret_cast<const bf16x8*>(kp + 32 * s);
+      *reinterpret_cast<bf16x8*>(stash_w + 16 * t * C::ROWB + ln.row + 512 * s) =
+          *reinterpret_cast<const bf16x8*>(vp + 32 * s);
+    }
+  }
+  f32x4 acc_k[C::DT][2], acc_v[C::DT][2];   // dK^T, dV^T
+#pragma unroll
+  for (int dt = 0; dt < C::DT; ++dt)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      acc_k[dt][t] = f32x4{};
+      acc_v[dt][t] = f32x4{};
+    }
+
+  // query runs of this unit, one per lane
+  int rn_len = 0, n_runs = 0;
+  uint64_t rn_q = 0, rn_g = 0, rn_l = 0, rn_d = 0;
+  auto set_run = [&](int i, int c0, int c1) {   // chunks c0 .. c1 - 1
+    if (lane == i) {
+      const int64_t t0 = int64_t(c0) * nq;
+      rn_len = (c1 - c0) * nq;
+      rn_q = reinterpret_cast<uint64_t>(q + t0 * row_elems + head * D);
+      rn_g = reinterpret_cast<uint64_t>(dout + t0 * row_elems + head * D);
+      rn_l = reinterpret_cast<uint64_t>(lse + t0 * heads + head);
+      rn_d = reinterpret_cast<uint64_t>(delta + t0 * heads + head);
+    }
+  };
+  if (is_chunk) {
+    set_run(0, owner, min(owner + min(plan.window, plan.n_chunks) + 1, plan.n_chunks));
+    n_runs = 1;
+  } else {
+    while (n_runs < 8 && ku.frame_runs[owner][2 * n_runs + 1] != 0) {
+      const int c0 = ku.frame_runs[owner][2 * n_runs];
+      set_run(n_runs, c0, c0 + ku.frame_runs[owner][2 * n_runs + 1]);
+      ++n_runs;
+    }
+  }
+  auto run_len = [&](int i) { return __builtin_amdgcn_readlane(rn_len, i); };
+  int n_tiles = 0;
+  for (int i = 0; i < n_runs; ++i) n_tiles += (run_len(i) + kRows - 1) / kRows;
+  Cursor c_t = {0, 0}, c_dma = {0, 0};
+  auto advance = [&](Cursor c) __attribute__((always_inline)) {
+    c.k0 += kRows;
+    if (c.k0 >= run_len(c.sg)) {
+      ++c.sg;
+      c.k0 = 0;
+    }
+    return c;
+  };
+  const uint32_t row_bytes = uint32_t(2 * row_elems);
+  auto issue_tile = [&](char* base, Cursor c) __attribute__((always_inline)) {
+    if (wave >= C::kCopyWaves) return;
+    const int last = run_len(c.sg) - 1 - c.k0;
+    const uint64_t off = uint64_t(c.k0) * row_bytes;
+    copy_tiles<D, kRows>(base, readlane_u64(rn_q, c.sg) + off, readlane_u64(rn_g, c.sg) + off, row_bytes,
+                         last, wave, lane);
+    // L, then D of the rows, 4 bytes per lane (one copy holds both of a 32-row tile)
+    if (wave < 2 * kRows / 64) {
+      const int i = 64 * wave + lane;
+      const uint64_t v = i < kRows ? readlane_u64(rn_l, c.sg) : readlane_u64(rn_d, c.sg);
+      lds_copy_dwords(uint32_t(size_t(LDS_PTR(char, base))) + C::SLOT + 256 * wave,
+                      v + uint64_t(c.k0 + min(i & (kRows - 1), last)) * uint32_t(4 * heads));
+    }
+  };
+
+  const float neg_inv_c = -1.0f / c_log2;
+  bf16x8 xq[C::KS][2];   // Q rows of the next tile
+  f32x4 p[2][2];         // [16-row half of the tile][16-key tile]: - L / c, S - L / c, then P
+  auto read_ahead = [&](const char* st, int kb) __attribute__((always_inline)) {
+    ln.read_rows(st, kb, xq);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const f32x4 Lr = *reinterpret_cast<const f32x4*>(st + C::SLOT + 4 * (32 * kb + 16 * h + 4 * grp)) * neg_inv_c;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) p[h][t] = Lr;
+    }
+  };
+  // block kb of the tile in st, whose Q rows have been read; (next, nkb): the block
+  // after it (in a stale slot after the last one: not used); nv: the block's rows
+  auto block = [&](const char* st, int kb, const char* next, int nkb, int nv) __attribute__((always_inline)) {
+    constexpr int kHalf = C::KS / 2;
+    f32x4 dp[2][2];
+    bf16x8 xg[C::KS][2], xv[C::KS][2];
+#pragma unroll
+    for (int s = 0; s < kHalf; ++s) {
+      ln.read_slice(st + C::TILE, kb, s, xg[s]);
+      ln.read_slice(stash_w, 0, s, xv[s]);
+    }
+#pragma unroll
+    for (int s = 0; s < C::KS; ++s)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          p[h][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xq[s][h], kreg[t][s], p[h][t], 0, 0, 0);
+    interleave<4 * C::KS, 4 * kHalf, 0, 0, 0>();
+    __builtin_amdgcn_sched_barrier(0);
+    if (nv < 32)   // rows past a run's end
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) p[h][t][j] = 4 * grp >= nv - 16 * h - j ? -INFINITY : p[h][t][j];
+#pragma unroll
+    for (int s = kHalf; s < C::KS; ++s) {
+      ln.read_slice(st + C::TILE, kb, s, xg[s]);
+      ln.read_slice(stash_w, 0, s, xv[s]);
+    }
+#pragma unroll
+    for (int s = 0; s < C::KS; ++s)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          dp[h][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xg[s][h], xv[s][t], s == 0 ? f32x4{} : dp[h][t], 0, 0, 0);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p[h][t][j] = __builtin_amdgcn_exp2f(p[h][t][j] * c_log2);
+    uint32_t pv[2][4], pk[2][4];
+    bf16x8 xc[C::DT], xk[C::DT];
+    ln.read_cols(st + C::TILE, kb, xc, 0, C::DT / 4);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < 4; j += 2) pv[t][2 * h + (j >> 1)] = pack_bf16(p[h][t][j], p[h][t][j + 1]);
+    interleave<4 * C::KS, 4 * (C::KS - kHalf) + C::DT / 2, 0, 24, 16>();
+    asm volatile("" ::"v"(pv[0][0]), "v"(pv[0][1]), "v"(pv[0][2]), "v"(pv[0][3]), "v"(pv[1][0]),
+                 "v"(pv[1][1]), "v"(pv[1][2]), "v"(pv[1][3]));
+    __builtin_amdgcn_sched_barrier(0);
+    {
+      ln.read_cols(st + C::TILE, kb, xc, C::DT / 4, C::DT);
+      ln.read_cols(st, kb, xk, 0, C::DT / 4);
+      ln.template product<2>(xc, pv, acc_v);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const f32x4 Dr = *reinterpret_cast<const f32x4*>(st + C::SLOT + 4 * (kRows + 32 * kb + 16 * h + 4 * grp));
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int j = 0; j < 4; j += 2)
+            pk[t][2 * h + (j >> 1)] = pack_bf16(p[h][t][j] * (dp[h][t][j] - Dr[j]),
+                                                p[h][t][j + 1] * (dp[h][t][j + 1] - Dr[j + 1]));
+      }
+      interleave<2 * C::DT, 2 * C::DT + 2, 0, 40, 0>();
+      asm volatile("" ::"v"(pk[0][0]), "v"(pk[0][1]), "v"(pk[0][2]), "v"(pk[0][3]), "v"(pk[1][0]),
+                   "v"(pk[1][1]), "v"(pk[1][2]), "v"(pk[1][3]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    {
+      ln.read_cols(st, kb, xk, C::DT / 4, C::DT);
+      ln.template product<2>(xk, pk, acc_k);
+      read_ahead(next, nkb);
+      interleave<2 * C::DT, 2 * C::DT - C::DT / 2 + 2 * C::KS + 2, 0, 16, 0>();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  auto slot = [&](int i) __attribute__((always_inline)) { return lds + i * kSlot; };
+  for (int i = 0; i < 3; ++i)
+    if (i < n_tiles) {
+      issue_tile(slot(i), c_dma);
+      c_dma = advance(c_dma);
+    }
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  __syncthreads();
+  if (idle) {   // only the copies and the barriers of the loop below
+    int i3 = 3;
+#pragma unroll 1
+    for (int t = 0; t < n_tiles; t += 2) {
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+      asm volatile("s_barrier" ::: "memory");
+      for (int i = 3; i < 5; ++i) {
+        if (t + i < n_tiles) {
+          issue_tile(slot(i3), c_dma);
+          c_dma = advance(c_dma);
+        }
+        i3 = i3 == 4 ? 0 : i3 + 1;
+      }
+    }
+    return;
+  }
+  read_ahead(slot(0), 0);
+  int i0 = 0;   // slot of tile t
+#pragma unroll 1
+  for (int t = 0; t < n_tiles; t += 2) {
+    const auto ahead = [&](int n) { return i0 + n >= 5 ? i0 + n - 5 : i0 + n; };
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+    for (int i = 3; i < 5; ++i)
+      if (t + i < n_tiles) {
+        issue_tile(slot(ahead(i)), c_dma);
+        c_dma = advance(c_dma);
+      }
+    auto tile = [&](const char* st, const char* next) __attribute__((always_inline)) {
+      const int nv = min(kRows, run_len(c_t.sg) - c_t.k0);
+      c_t = advance(c_t);
+      if constexpr (kBlocks == 2) block(st, 0, st, 1, nv);
+      block(st, kBlocks - 1, next, 0, nv - 32 * (kBlocks - 1));
+    };
+    tile(slot(i0), slot(ahead(1)));
+    if (t + 1 < n_tiles) tile(slot(ahead(1)), slot(ahead(2)));
+    i0 = ahead(2);
+  }
+
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int key = k0 + 16 * t + l16;
+    if (key < n_keys) {
+      __bf16* pk = obase_k + key * row_elems + 4 * grp;
+      __bf16* pv = obase_v + key * row_elems + 4 * grp;
+#pragma unroll
+      for (int dt = 0; dt < C::DT; ++dt) {
+        u32x2 w;
+        w.x = pack_bf16(acc_k[dt][t][0] * scale, acc_k[dt][t][1] * scale);
+        w.y = pack_bf16(acc_k[dt][t][2] * scale, acc_k[dt][t][3] * scale);
+        *reinterpret_cast<u32x2*>(pk + 16 * dt) = w;
+        w.x = pack_bf16(acc_v[dt][t][0], acc_v[dt][t][1]);
+        w.y = pack_bf16(acc_v[dt][t][2], acc_v[dt][t][3]);
+        *reinterpret_cast<u32x2*>(pv + 16 * dt) = w;
+      }
+    }
   }
 }
 
@@ -815,11 +780,11 @@ void bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ dou
 // or 0 where the 256-row kernels of this file are the better ones: the shortest
 // estimate, per pass, of a fixed part plus the 64-row tiles that the busiest CU
 // streams (an even share of all and a third of the longest stream, at least the
-// longest one) times the time of one.  The constants are fits to 30 launches of
+// longest one) times the time of one.  The constants are fits to 45 launches of
 // 1 to 40 heads, 3 to 27 chunks of 63 to 2016 tokens, each form forced (us of
 // the whole backward, 256-row kernels / split dQ / split dK and dV: 6 heads x 64,
-// 7 chunks of 351 tokens 119 / 98 / 78; 1 head x 128, 18 x 432 386 / 328 / 143;
-// 24 heads x 128, 11 x 1056, which fills the GPU, 2479 / 2551 / 2743).
+// 7 chunks of 351 tokens 104 / 96 / 74; 24 heads x 128, 11 x 1056, which fills the
+// GPU, 2020 / 2220 / 2290).
 struct SplitChoice {
   int q, k;   // dQ; dK and dV
 };
@@ -836,10 +801,10 @@ SplitChoice choose_split(const PackedPlan& plan, int heads, int head_dim, const 
   };
   constexpr double kMargin = 0.92;   // near a tie the 256-row kernels, which read less
   const bool wide = head_dim == 128;
-  const Cost cost_q[3] = {wide ? Cost{4.0, 2.93} : Cost{4.0, 1.89}, wide ? Cost{4.5, 0.46} : Cost{8.0, 0.25},
-                          wide ? Cost{4.5, 0.68} : Cost{8.0, 0.37}};
-  const Cost cost_k[3] = {wide ? Cost{4.0, 3.33} : Cost{8.0, 1.64}, wide ? Cost{4.0, 0.49} : Cost{10.0, 0.27},
-                          wide ? Cost{4.0, 0.49} : Cost{10.0, 0.32}};
+  const Cost cost_q[3] = {wide ? Cost{4.0, 2.40} : Cost{4.0, 1.60}, wide ? Cost{6.0, 0.43} : Cost{7.0, 0.22},
+                          wide ? Cost{7.0, 0.59} : Cost{6.0, 0.32}};
+  const Cost cost_k[3] = {wide ? Cost{4.0, 2.70} : Cost{6.0, 1.75}, wide ? Cost{8.0, 0.46} : Cost{8.0, 0.27},
+                          wide ? Cost{8.0, 0.46} : Cost{8.0, 0.32}};
   const int nq = plan.chunk_tokens, n = plan.n_chunks;
   const int window = plan.window < n ? plan.window : n;
   const auto groups = [](int rows, int per) { return double((rows + per - 1) / per); };
@@ -921,10 +886,10 @@ hipError_t launch_attention_bwd_bf16(const void* q, const void* out, const void*
                                              softmax_scale, plan, stream);
     if (e != hipSuccess) return e;
   } else if (head_dim == 128) {
-    hipLaunchKernelGGL((bwd_dq_kernel<128, 3>), g_q, dim3(kThreads), 0, stream, qp, dp, lse, delta,
+    hipLaunchKernelGGL((bwd_dq_kernel<128>), g_q, dim3(kThreads), 0, stream, qp, dp, lse, delta,
                        static_cast<__bf16*>(dq), heads, c_log2, softmax_scale, plan, n_qtiles);
   } else {
-    hipLaunchKernelGGL((bwd_dq_kernel<64, 4>), g_q, dim3(kThreads), 0, stream, qp, dp, lse, delta,
+    hipLaunchKernelGGL((bwd_dq_kernel<64>), g_q, dim3(kThreads), 0, stream, qp, dp, lse, delta,
                        static_cast<__bf16*>(dq), heads, c_log2, softmax_scale, plan, n_qtiles);
   }
   if (split.k) {
@@ -932,10 +897,10 @@ hipError_t launch_attention_bwd_bf16(const void* q, const void* out, const void*
                                               head_dim, softmax_scale, plan, frame_runs, n_frames, stream);
     if (e != hipSuccess) return e;
   } else if (head_dim == 128) {
-    hipLaunchKernelGGL((bwd_dkv_kernel<128, 4, 32>), g_k, dim3(kThreads), 0, stream, qp, dp, lse,
+    hipLaunchKernelGGL((bwd_dkv_kernel<128>), g_k, dim3(kThreads), 0, stream, qp, dp, lse,
                        delta, dkp, dakp, dvp, davp, heads, c_log2, softmax_scale, plan, ku);
   } else {
-    hipLaunchKernelGGL((bwd_dkv_kernel<64, 4, 64>), g_k, dim3(kThreads), 0, stream, qp, dp, lse,
+    hipLaunchKernelGGL((bwd_dkv_kernel<64>), g_k, dim3(kThreads), 0, stream, qp, dp, lse,
                        delta, dkp, dakp, dvp, davp, heads, c_log2, softmax_scale, plan, ku);
   }
   return hipGetLastError();

@@ -25,8 +25,11 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // for explicitly (vmcnt) before the copied bytes are read.
 template <int N>
 __device__ inline void lds_copy_blocks(uint32_t dst, const char* base, const uint32_t (&off)[N]) {
-  static_assert(N == 2 || N == 4, "two or four 1 KB copies per wave and tensor");
-  if constexpr (N == 2)
+  static_assert(N == 1 || N == 2 || N == 4, "1 KB copies per wave and tensor");
+  if constexpr (N == 1)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(dst), "v"(off[0]), "s"(base) : "memory");
+  else if constexpr (N == 2)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                  "global_load_lds_dwordx4 %1, %3\n\t"
                  "global_load_lds_dwordx4 %2, %3 offset:1024"

@@ -18,6 +18,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <iterator>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -157,6 +158,7 @@ struct ff_cache {
   ff_cache_desc desc;
   Layout layout;
   char* dev;  // caller-owned device buffer
+  double omega[64];  // RoPE frequency of each pair
   // ring bookkeeping per (stage, layer): slot -> chunk (-1 empty), next chunk (-1 unset)
   std::vector<int64_t> slot_chunk;
   std::vector<int64_t> next_chunk;
@@ -273,6 +275,12 @@ ff_status ff_cache_create(const ff_cache_desc* desc, void* dev_buf, size_t dev_b
     c->desc = rd;
     c->layout = L;
     c->dev = static_cast<char*>(dev_buf);
+    const int axis_n[3] = {rd.rope_pairs_t, rd.rope_pairs_h, rd.rope_pairs_w};
+    std::fill(std::begin(c->omega), std::end(c->omega), 0.0);
+    int pair = 0;
+    for (int a = 0; a < 3; ++a)
+      for (int j = 0; j < axis_n[a]; ++j)
+        c->omega[pair++] = std::pow(rd.rope_theta, -double(j) / double(axis_n[a]));
     const size_t rings = size_t(rd.num_stages) * rd.num_layers;
     c->slot_chunk.assign(rings * rd.ring_chunks, -1);
     c->next_chunk.assign(rings, -1);
@@ -312,11 +320,7 @@ ff_status ff_rope3d(const ff_cache* cache, void* q, void* k, int32_t n_frames,
   }
   p.n_t = d.rope_pairs_t;
   p.n_th = d.rope_pairs_t + d.rope_pairs_h;
-  const int axis_n[3] = {d.rope_pairs_t, d.rope_pairs_h, d.rope_pairs_w};
-  int pair = 0;
-  for (int a = 0; a < 3; ++a)
-    for (int j = 0; j < axis_n[a]; ++j)
-      p.omega[pair++] = std::pow(d.rope_theta, -double(j) / double(axis_n[a]));
+  std::copy(std::begin(cache->omega), std::end(cache->omega), p.omega);
   const int n_tok = n_frames * d.grid_h * d.grid_w;
   hipError_t e = ff::launch_rope3d(q, k, n_tok, d.num_heads, d.head_dim, d.dtype, d.grid_w,
                                    d.grid_h * d.grid_w, p, static_cast<hipStream_t>(stream));
@@ -1009,7 +1013,9 @@ ff_status ff_wavefront_run(int64_t n_chunks, int32_t n_stages, void* const* stre
           break;
         }
         ++forwards;
-        if (hipEventRecord(done[s], hs) != hipSuccess) st = fail(FF_ERR_HIP, "hipEventRecord failed");
+        // (nothing waits on the last rank)
+        if (s + 1 < n_stages && hipEventRecord(done[s], hs) != hipSuccess)
+          st = fail(FF_ERR_HIP, "hipEventRecord failed");
       }
     }
     if (st != FF_OK) return st;

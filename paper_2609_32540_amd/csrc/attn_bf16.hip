@@ -195,6 +195,10 @@ void attn_bf16_kernel(const __bf16* __restrict__ q, __bf16* __restrict__ out, in
   if constexpr (kSets) {
     chunk = logical / (heads * n_qtiles);
     rest = logical - chunk * (heads * n_qtiles);
+    // the first chunks of a clip have short read sets: they run last, where they
+    // fill the last round better (training step of 27 chunks of 4680 tokens 75.4
+    // -> 74.3 ms, with the same order in the dQ kernel)
+    if constexpr (kPacked) chunk = src.n_chunks - 1 - chunk;
   }
   if constexpr (kPacked) {
     q += int64_t(chunk) * nq * heads * D;

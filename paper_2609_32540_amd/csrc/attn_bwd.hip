@@ -242,8 +242,9 @@ void bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ dout
   __shared__ __attribute__((aligned(1024))) char lds[5 * C::SLOT];
   const int nq = plan.chunk_tokens;
   const int logical = xcd_interleaved(blockIdx.x, gridDim.x, n_qtiles);
-  const int chunk = logical / (heads * n_qtiles);
-  const int rest = logical - chunk * heads * n_qtiles;
+  const int nth = logical / (heads * n_qtiles);
+  const int chunk = plan.n_chunks - 1 - nth;   // the first chunks' short read sets run last
+  const int rest = logical - nth * heads * n_qtiles;
   const int head = rest / n_qtiles, qt = rest % n_qtiles;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, l16 = lane & 15, grp = lane >> 4;

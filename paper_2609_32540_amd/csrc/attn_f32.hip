@@ -51,7 +51,7 @@ constexpr int kXcds = 8;
 template <int D, int QT, class Src>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, int nq, int heads,
-                     float scale_log2, Src src, int n_qtiles) {
+                     float scale, Src src, int n_qtiles) {
   constexpr bool kPacked = __is_same(Src, PackedPlan);
   constexpr bool kBatch = __is_same(Src, KvBatch);
   constexpr bool kSets = kPacked || kBatch;
@@ -97,8 +97,9 @@ void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, int n
   for (int t = 0; t < QT; ++t) {
     const float* qp = q + (int64_t(min(q0 + 16 * t + l16, nq - 1)) * heads + head) * D + 4 * grp;
 #pragma unroll
-    for (int i = 0; i < KT; ++i) qreg[t][i] = *reinterpret_cast<const f32x4*>(qp + 16 * i);
+    for (int i = 0; i < KT; ++i) qreg[t][i] = *reinterpret_cast<const f32x4*>(qp + 16 * i) * scale;
   }
+  constexpr float kLog2e = 1.44269504f;
   f32x4 o[QT][VH][4];
   float m_run[QT], l_run[QT];
 #pragma unroll
@@ -134,7 +135,8 @@ void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, int n
     }
   };
   f32x4 kreg[KT], vreg[4][VH];
-  // rows past the segment's end re-read its last row (their scores are masked)
+  // rows past the segment's end re-read its last row (their scores are masked,
+  // their V is zeroed)
   auto load_k = [&]() __attribute__((always_inline)) {
     const int row = min(blk * kBK + l16, seg.len - 1);
     const float* p = static_cast<const float*>(seg.k) + head * seg.head_stride +
@@ -187,7 +189,7 @@ void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, int n
 #pragma unroll
         for (int j = 0; j < 4; ++j) s[t][j] = 4 * grp + j < n_valid ? s[t][j] : -INFINITY;
       float mx = fmaxf(fmaxf(s[t][0], s[t][1]), fmaxf(s[t][2], s[t][3]));
-      mx = fmaxf(m_run[t], max_across_groups(mx) * scale_log2);
+      mx = fmaxf(m_run[t], max_across_groups(mx) * kLog2e);
       alpha[t] = __builtin_amdgcn_exp2f(m_run[t] - mx);
       raised |= mx != m_run[t];
       m_run[t] = mx;
@@ -206,9 +208,15 @@ void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, int n
     for (int t = 0; t < QT; ++t) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        s[t][j] = __builtin_amdgcn_exp2f(fmaf(s[t][j], scale_log2, -m_run[t]));
+        s[t][j] = __builtin_amdgcn_exp2f(fmaf(s[t][j], kLog2e, -m_run[t]));
       l_run[t] += (s[t][0] + s[t][1]) + (s[t][2] + s[t][3]);
     }
+    if (n_valid < kBK)   // (probability 0 times an infinite last row would be NaN)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (4 * grp + j >= n_valid)
+#pragma unroll
+          for (int h = 0; h < VH; ++h) vreg[j][h] = f32x4{};
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -272,12 +280,11 @@ template <class Src>
 hipError_t launch(const float* q, float* out, int nq, int heads, int head_dim, float softmax_scale,
                   const Src& src, int sets, hipStream_t stream) {
   if (nq <= 0 || sets <= 0) return hipSuccess;
-  const float c = float(double(softmax_scale) * 1.4426950408889634);
   const int qt = query_tiles(nq, heads, sets);
   const int n_qtiles = (nq + 16 * qt - 1) / (16 * qt);
   const dim3 grid(unsigned(n_qtiles * heads * sets));
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, q, out, nq, heads, c, src, n_qtiles);
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, q, out, nq, heads, softmax_scale, src, n_qtiles);
     return hipGetLastError();
   };
   if (head_dim == 64)

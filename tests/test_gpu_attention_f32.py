@@ -72,3 +72,31 @@ def test_flat_and_peaked_rows(scale):
         assert err.max() <= bar and np.linalg.norm(err) <= bar * np.linalg.norm(ref)
         cache.kv_publish(0, 0, c, to_dev(k), to_dev(v))
         oracle.publish(0, 0, c, exact(k), exact(v))
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_infinite_value_in_a_segments_last_row(head_dim):
+    # 27-token chunks end inside a 16-key block: its missing keys must add nothing, also where
+    # the last row of V, which their addresses repeat, is infinite
+    w = small("f32", head_dim, grid_h=3, grid_w=3, stages=1, layers=1, n_chunks=2)
+    cache = make_cache(w, 1, 1)
+    q, k, v = (to_dev(synth.chunk_tensor(w, t, 0, 0, 0)) for t in (synth.T_Q, synth.T_K, synth.T_V))
+    v[-1, :, 3] = float("inf")
+    out = cache.chunk_attention(0, 0, 0, q, k, v)
+    assert torch.isinf(out[:, :, 3]).all()
+    keep = [e for e in range(head_dim) if e != 3]
+    oracle = make_oracle(w, 1, 1)
+    vv = exact(v)
+    vv[-1, :, 3] = 0.0
+    ref = oracle.attention(0, 0, 0, exact(q), exact(k), vv)
+    check_attention(exact(out)[..., keep], ref[..., keep], "f32")
+
+
+def test_scores_are_scaled_before_they_are_summed():
+    # |q.k| would pass the float32 range, scale * |q.k| does not
+    w = small("f32", 64, grid_h=3, grid_w=3, stages=1, layers=1, n_chunks=2)
+    cache, oracle = make_cache(w, 1, 1), make_oracle(w, 1, 1)
+    q, k, v = (synth.chunk_tensor(w, t, 0, 0, 0) for t in (synth.T_Q, synth.T_K, synth.T_V))
+    out = cache.chunk_attention(0, 0, 0, to_dev(q * 1e20), to_dev(k * 1e20), to_dev(v), scale=2.0 ** -135)
+    ref = oracle.attention(0, 0, 0, exact(q * 1e20), exact(k * 1e20), exact(v), scale=2.0 ** -135)
+    check_attention(exact(out), ref, "f32")

@@ -25,9 +25,9 @@
 // operand of the next product as bf16 (nearest even).  Against the 32x32x16
 // kernels before them, at 12 heads x 128, 27 chunks of 4680 tokens (one box,
 // whole training step 86.2 ms -> 77.9 ms): dQ with dO in LDS, products and VALU
-// work in sequence 28.8 ms -> 25.2 ms; dK and dV 38.5 ms -> 34.0 ms, of which the
-// operands read one region ahead give 1.6 ms and waves without rows, which skip
-// the products of a ragged last tile, 0.8 ms together.
+// work in sequence 28.8 ms -> 25.2 ms; dK and dV 38.5 ms -> 34.0 ms.  Of the step's
+// time, reading dK/dV's operands one region ahead saves 1.6 ms, waves without rows
+// skipping the products of a ragged last tile 1.2 ms.
 
 #include <hip/hip_runtime.h>
 

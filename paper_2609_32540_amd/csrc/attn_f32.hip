@@ -28,7 +28,7 @@
 //
 // Against the kernel before it (one thread per query, fma from LDS, one
 // workgroup per 128 queries): 12 heads x 128, 1170 queries over 7020 keys 14.4
-// ms -> 0.56 ms (90 of the 153 TFLOP/s a large float32 product reaches here;
+// ms -> 0.52 ms (97 of the 153 TFLOP/s a large float32 product reaches here;
 // 444 workgroups are 1.73 rounds of 256 CUs); 2 heads x 64, 192 queries over
 // 704 keys 545 us -> 12 us.  Error against float64 5.5e-7 (1.9e-6 before:
 // shorter sums).

@@ -28,13 +28,17 @@
 //
 // Against the kernel before it (one thread per query, fma from LDS, one
 // workgroup per 128 queries): 12 heads x 128, 1170 queries over 7020 keys 14.4
-// ms -> 0.52 ms (97 of the 153 TFLOP/s a large float32 product reaches here;
+// ms -> 0.54 ms (93 of the 153 TFLOP/s a large float32 product reaches here;
 // 444 workgroups are 1.73 rounds of 256 CUs); 2 heads x 64, 192 queries over
 // 704 keys 545 us -> 12 us.  Error against float64 5.5e-7 (1.9e-6 before:
-// shorter sums).
+// shorter sums).  The max is subtracted from a score before the factor log2 e
+// is applied (one fma for both is 3% faster): the largest key's exponent is
+// then exactly 0, where the fma would leave the rounding error of max * log2 e,
+// which from scores of about 3e9 passes the float32 exponent range.
 
 #include <hip/hip_runtime.h>
 
+#include <float.h>
 #include <math.h>
 
 #include "attn_tile.h"
@@ -47,6 +51,7 @@ constexpr int kWaves = 8;                 // key groups of a workgroup
 constexpr int kThreads = 64 * kWaves;
 constexpr int kBK = 16;                   // keys per block
 constexpr int kXcds = 8;
+constexpr float kLog2e = 1.44269504f;
 
 template <int D, int QT, class Src>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -99,12 +104,11 @@ void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, int n
 #pragma unroll
     for (int i = 0; i < KT; ++i) qreg[t][i] = *reinterpret_cast<const f32x4*>(qp + 16 * i) * scale;
   }
-  constexpr float kLog2e = 1.44269504f;
   f32x4 o[QT][VH][4];
   float m_run[QT], l_run[QT];
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
-    m_run[t] = -INFINITY;
+    m_run[t] = -FLT_MAX;   // (finite: a key whose score is -inf then gets weight 0)
     l_run[t] = 0.0f;
 #pragma unroll
     for (int h = 0; h < VH; ++h)
@@ -189,8 +193,8 @@ void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, int n
 #pragma unroll
         for (int j = 0; j < 4; ++j) s[t][j] = 4 * grp + j < n_valid ? s[t][j] : -INFINITY;
       float mx = fmaxf(fmaxf(s[t][0], s[t][1]), fmaxf(s[t][2], s[t][3]));
-      mx = fmaxf(m_run[t], max_across_groups(mx) * kLog2e);
-      alpha[t] = __builtin_amdgcn_exp2f(m_run[t] - mx);
+      mx = fmaxf(m_run[t], max_across_groups(mx));
+      alpha[t] = __builtin_amdgcn_exp2f((m_run[t] - mx) * kLog2e);
       raised |= mx != m_run[t];
       m_run[t] = mx;
     }
@@ -208,7 +212,7 @@ void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, int n
     for (int t = 0; t < QT; ++t) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        s[t][j] = __builtin_amdgcn_exp2f(fmaf(s[t][j], kLog2e, -m_run[t]));
+        s[t][j] = __builtin_amdgcn_exp2f((s[t][j] - m_run[t]) * kLog2e);
       l_run[t] += (s[t][0] + s[t][1]) + (s[t][2] + s[t][3]);
     }
     if (n_valid < kBK)   // (probability 0 times an infinite last row would be NaN)
@@ -257,7 +261,7 @@ void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, int n
     f32x4 acc = {};
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      const float a = __builtin_amdgcn_exp2f(part_m[w * kRows + r] - m);
+      const float a = __builtin_amdgcn_exp2f((part_m[w * kRows + r] - m) * kLog2e);
       l += a * part_l[w * kRows + r];
       acc += a * *reinterpret_cast<const f32x4*>(part + (w * kRows + r) * kPitch + 4 * c);
     }

@@ -100,3 +100,39 @@ def test_scores_are_scaled_before_they_are_summed():
     out = cache.chunk_attention(0, 0, 0, to_dev(q * 1e20), to_dev(k * 1e20), to_dev(v), scale=2.0 ** -135)
     ref = oracle.attention(0, 0, 0, exact(q * 1e20), exact(k * 1e20), exact(v), scale=2.0 ** -135)
     check_attention(exact(out), ref, "f32")
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_very_large_scores(head_dim):
+    # scores of about 1e10 times N(0, 1): each row is one-hot on its largest key (float32 sums
+    # of 64 to 128 products are off by under 1e5 there, the two largest of 27 to 81 scores are
+    # 1e6 or more apart), so the output is that key's row of V to float32 rounding
+    w = small("f32", head_dim, grid_h=3, grid_w=3, stages=1, layers=1, n_chunks=3)
+    cache, hist = make_cache(w, 1, 1), []
+    for c in range(w.n_chunks):
+        q, k, v = (synth.chunk_tensor(w, t, c, 0, 0) for t in (synth.T_Q, synth.T_K, synth.T_V))
+        q = q * 1e10
+        out = exact(cache.chunk_attention(0, 0, c, to_dev(q), to_dev(k), to_dev(v)))
+        hist.append((k.double(), v))
+        K, V = (torch.cat([h[i] for h in hist]) for i in (0, 1))
+        s = torch.einsum("qhd,khd->hqk", q.double(), K) / head_dim ** 0.5
+        top = s.topk(2, dim=2)
+        assert float((top.values[..., 0] - top.values[..., 1]).min()) > 1e6
+        ref = torch.stack([V[top.indices[h, :, 0], h] for h in range(w.heads)], 1)
+        np.testing.assert_allclose(out, ref.numpy(), rtol=1e-6, atol=0)
+        cache.kv_publish(0, 0, c, to_dev(k), to_dev(v))
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_blocks_of_keys_that_score_minus_infinity(head_dim):
+    # products past the float32 range: whole 16-key blocks, the read set's first one and the
+    # first of several waves among them, score -inf for every query and get weight 0
+    w = small("f32", head_dim, grid_h=6, grid_w=11, stages=1, layers=1, n_chunks=1)
+    cache, oracle = make_cache(w, 1, 1), make_oracle(w, 1, 1)
+    q, k, v = (synth.chunk_tensor(w, t, 0, 0, 0) for t in (synth.T_Q, synth.T_K, synth.T_V))
+    q[:, :, 0] = 1e25
+    k[:, :, 0] = 0.0
+    dead = np.r_[0:16, 48:80, 128:144]
+    k[dead, :, 0] = -1e25
+    out = cache.chunk_attention(0, 0, 0, to_dev(q), to_dev(k), to_dev(v))
+    check_attention(exact(out), oracle.attention(0, 0, 0, exact(q), exact(k), exact(v)), "f32")

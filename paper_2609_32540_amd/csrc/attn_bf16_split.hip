@@ -21,6 +21,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <float.h>
 #include <math.h>
 
 #include "attn_tile.h"
@@ -97,7 +98,7 @@ void attn_bf16_split_kernel(const __bf16* __restrict__ q, __bf16* __restrict__ o
   float m_run[QT], l_run[QT];
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
-    m_run[t] = -INFINITY;    // set by the first block; a wave without keys keeps weight 0
+    m_run[t] = -FLT_MAX;     // set by the first block; finite: keys that score -inf get weight 0
     l_run[t] = 0.0f;
 #pragma unroll
     for (int dt = 0; dt < C::DT; ++dt) o[dt][t] = f32x4{};

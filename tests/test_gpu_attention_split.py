@@ -95,6 +95,23 @@ def test_packed_with_log_sum_exp(head_dim, grid):
         np.testing.assert_allclose(exact(lse[c * nq:(c + 1) * nq]), want, atol=1e-4)
 
 
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_blocks_of_keys_that_score_minus_infinity(head_dim):
+    # products past the float32 range: whole 32-key blocks, the first one of several waves
+    # among them (and, in the second call, the read set's first), score -inf for every query
+    # and get weight 0
+    w = small("bf16", head_dim, grid_h=6, grid_w=11, stages=1, layers=1, n_chunks=1)
+    q, k, v = (synth.chunk_tensor(w, t, 0, 0, 0) for t in (synth.T_Q, synth.T_K, synth.T_V))
+    q[:, :, 0] = 1e25
+    k[:, :, 0] = 0.0
+    for dead in (np.r_[32:64, 96:160], np.r_[0:64, 192:198]):
+        kk = k.clone()
+        kk[dead, :, 0] = -1e25
+        cache, oracle = make_cache(w, 1, 1), make_oracle(w, 1, 1)
+        out = cache.chunk_attention(0, 0, 0, to_dev(q), to_dev(kk), to_dev(v))
+        check_attention(exact(out), oracle.attention(0, 0, 0, exact(q), exact(kk), exact(v)), "bf16")
+
+
 # the smallest launches left to the 256-query kernel, whose partial last round runs as 2, 3
 # and 4 key parts: 96, 80 and 60 units on 256 CUs
 @pytest.mark.parametrize("heads,grid,head_dim", [(24, (12, 22), 128), (24, (12, 22), 64),

@@ -3,8 +3,8 @@
 // queries and split the keys.
 //
 // Work split: a workgroup = 8 waves = QT tiles of 16 queries of one head, the
-// key blocks (32 keys) dealt round robin to the waves, each with its own
-// reference max, sum and O; the eight partial results are merged through LDS.
+// key blocks (32 keys) dealt round robin to the waves, each with its own sum and
+// O; the eight partial results are merged through LDS.
 // A launch has heads * ceil(nq / 16 QT) workgroups, 8 to 16 times those of the
 // 256-query kernel, and a wave's serial chain is an eighth of the keys.  In
 // exchange every workgroup reads all of its head's K and V (the 256-query
@@ -17,7 +17,17 @@
 // and V operands into registers before its products, which frees the LDS for
 // the next block's copy: that copy runs under this block's products and
 // softmax, and one 16 KB pair per wave is all the LDS a wave needs.  Nothing is
-// shared between waves inside the key loop, so it has no barrier.
+// shared between waves inside the key loop but the first block's max, so it has
+// one barrier, in each wave's first step.
+//
+// Rounding.  Every wave starts from the reference max of the 256-query kernel,
+// the column max of the read set's first 32 keys (wave 0's first block), so each
+// probability is rounded to bf16 relative to the same reference as there, and
+// O is divided by the same sums.  A query's reference moves by its own scores
+// only: its result does not depend on which queries share its workgroup, nor on
+// QT.  Against a reference of each wave's own this costs 1 us of 8.2 (2 heads x
+// 128, 198 queries over 726 keys) and of 18.8 (6 heads x 64, packed clip of 7 x
+// 351 tokens).
 
 #include <hip/hip_runtime.h>
 
@@ -34,7 +44,8 @@ constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kBK = 32;                  // keys per block
 constexpr int kXcds = 8;
-constexpr float kRaise = 4.0f;           // log2 units the column max may exceed the reference by
+constexpr float kRaise = 56.0f;          // log2 units the column max may exceed the reference by:
+                                         // sums of 2^56 times the keys stay far inside float32
 
 template <int D, int QT>
 struct SplitCfg {
@@ -57,6 +68,7 @@ void attn_bf16_split_kernel(const __bf16* __restrict__ q, __bf16* __restrict__ o
   constexpr bool kSets = kPacked || kBatch;
   using C = SplitCfg<D, QT>;
   __shared__ __attribute__((aligned(1024))) char lds[C::kLds];
+  __shared__ float ref_max[C::kRows];
 
   // as in attn_f32.hip: contiguous ranges of workgroups per XCD, or whole
   // (set, head) pairs round robin when the sets' lengths differ
@@ -96,10 +108,12 @@ void attn_bf16_split_kernel(const __bf16* __restrict__ q, __bf16* __restrict__ o
   }
   f32x4 o[C::DT][QT];
   float m_run[QT], l_run[QT];
+  f32x4 lsum[QT];            // row sums (every row of the tile holds the sum)
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
-    m_run[t] = -FLT_MAX;     // set by the first block; finite: keys that score -inf get weight 0
+    m_run[t] = -FLT_MAX;     // (finite: keys that score -inf get weight 0)
     l_run[t] = 0.0f;
+    lsum[t] = f32x4{};
 #pragma unroll
     for (int dt = 0; dt < C::DT; ++dt) o[dt][t] = f32x4{};
   }
@@ -178,10 +192,47 @@ void attn_bf16_split_kernel(const __bf16* __restrict__ q, __bf16* __restrict__ o
     return last + 1;
   };
 
+  // S^T of a block from its K operands (rows 16 kh + l16, d slice ks), keys past
+  // n_valid masked, and the column max of each query
+  auto scores = [&](const bf16x8 (&kc)[2][C::KS], int n_valid, f32x4 (&s)[2][QT], float (&mx)[QT])
+      __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < C::KS; ++ks)
+#pragma unroll
+      for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+        for (int t = 0; t < QT; ++t)
+          s[kh][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kc[kh][ks], qreg[t][ks],
+                                                             ks == 0 ? f32x4{} : s[kh][t], 0, 0, 0);
+    if (n_valid < kBK)
+#pragma unroll
+      for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+        for (int t = 0; t < QT; ++t)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            s[kh][t][j] = 4 * grp >= n_valid - 16 * kh - j ? -INFINITY : s[kh][t][j];
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      mx[t] = fmaxf(fmaxf(s[0][t][0], s[0][t][1]), fmaxf(s[0][t][2], s[0][t][3]));
+      mx[t] = fmaxf(mx[t], fmaxf(fmaxf(s[1][t][0], s[1][t][1]), fmaxf(s[1][t][2], s[1][t][3])));
+      mx[t] = max_across_groups(mx[t]) * scale_log2;
+    }
+  };
+
+  // The barrier behind wave 0's reference max, which every wave passes once: in
+  // its first step or, without a block, before the merge.  (Written out: copies
+  // in flight need no wait.)
+  auto publish_barrier = []() __attribute__((always_inline)) {
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the max is written
+    asm volatile("s_barrier" ::: "memory");
+  };
+
   // One block: take its K and V into registers, start the copy of the next one
   // into their place (when there is one), then S^T, softmax and O^T.  Returns
-  // the next block's valid keys, 0 without one.
-  auto step = [&](int n_valid) __attribute__((always_inline)) {
+  // the next block's valid keys, 0 without one.  The wave's first step also takes
+  // the reference max from wave 0, whose first block is the read set's.
+  auto step = [&](int n_valid, bool first) __attribute__((always_inline)) {
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
     asm volatile("" ::: "memory");
     bf16x8 kc[2][C::KS], va[C::DT];
@@ -204,38 +255,28 @@ void attn_bf16_split_kernel(const __bf16* __restrict__ q, __bf16* __restrict__ o
     const int nv_next = settle() ? fetch() : 0;
     __builtin_amdgcn_sched_barrier(0);
     f32x4 s[2][QT];
-#pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks)
-#pragma unroll
-      for (int kh = 0; kh < 2; ++kh)
-#pragma unroll
-        for (int t = 0; t < QT; ++t)
-          s[kh][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kc[kh][ks], qreg[t][ks],
-                                                             ks == 0 ? f32x4{} : s[kh][t], 0, 0, 0);
-    if (n_valid < kBK)
-#pragma unroll
-      for (int kh = 0; kh < 2; ++kh)
-#pragma unroll
-        for (int t = 0; t < QT; ++t)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            s[kh][t][j] = 4 * grp >= n_valid - 16 * kh - j ? -INFINITY : s[kh][t][j];
-    // the reference max follows the column max once that is kRaise above it
-    bool over = false;
     float mx[QT];
+    scores(kc, n_valid, s, mx);
+    if (first) {
+      if (wave == 0 && grp == 0) {
 #pragma unroll
-    for (int t = 0; t < QT; ++t) {
-      mx[t] = fmaxf(fmaxf(s[0][t][0], s[0][t][1]), fmaxf(s[0][t][2], s[0][t][3]));
-      mx[t] = fmaxf(mx[t], fmaxf(fmaxf(s[1][t][0], s[1][t][1]), fmaxf(s[1][t][2], s[1][t][3])));
-      mx[t] = max_across_groups(mx[t]) * scale_log2;
-      over |= mx[t] > m_run[t] + kRaise;
+        for (int t = 0; t < QT; ++t) ref_max[16 * t + l16] = mx[t];
+      }
+      publish_barrier();
+#pragma unroll
+      for (int t = 0; t < QT; ++t) m_run[t] = fmaxf(ref_max[16 * t + l16], -FLT_MAX);
     }
+    // a query's reference follows its column max once that is kRaise above it
+    bool over = false;
+#pragma unroll
+    for (int t = 0; t < QT; ++t) over |= mx[t] > m_run[t] + kRaise;
     if (__builtin_amdgcn_ballot_w64(over) != 0) {
 #pragma unroll
       for (int t = 0; t < QT; ++t) {
-        const float m_new = fmaxf(m_run[t], mx[t]);
+        const float m_new = mx[t] > m_run[t] + kRaise ? mx[t] : m_run[t];
         const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_new);
         l_run[t] *= alpha;
+        lsum[t] *= alpha;
         m_run[t] = m_new;
 #pragma unroll
         for (int dt = 0; dt < C::DT; ++dt)
@@ -254,10 +295,13 @@ void attn_bf16_split_kernel(const __bf16* __restrict__ q, __bf16* __restrict__ o
           const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kh][t][j], scale_log2, -m_run[t]));
           const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kh][t][j + 1], scale_log2, -m_run[t]));
           pk[t][2 * kh + (j >> 1)] = pack_bf16(p0, p1);
-          lb += p0 + p1;
+          if constexpr (kPacked) lb += p0 + p1;
         }
       l_run[t] += lb;
     }
+    // (all ones: every row of the result is the column sum of P^T)
+    const bf16x8 ones = {__bf16(1.0f), __bf16(1.0f), __bf16(1.0f), __bf16(1.0f),
+                         __bf16(1.0f), __bf16(1.0f), __bf16(1.0f), __bf16(1.0f)};
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
       const u32x4 pu = {pk[t][0], pk[t][1], pk[t][2], pk[t][3]};
@@ -265,11 +309,14 @@ void attn_bf16_split_kernel(const __bf16* __restrict__ q, __bf16* __restrict__ o
 #pragma unroll
       for (int dt = 0; dt < C::DT; ++dt)
         o[dt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[dt], pb, o[dt][t], 0, 0, 0);
+      lsum[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb, lsum[t], 0, 0, 0);
     }
     return nv_next;
   };
 
-  for (int nv = settle() ? fetch() : 0; nv > 0;) nv = step(nv);
+  int nv = settle() ? fetch() : 0;
+  if (nv == 0) publish_barrier();
+  for (bool first = true; nv > 0; first = false) nv = step(nv, first);
 
   // merge the waves' partial results (over the K and V blocks, once all are read)
   __syncthreads();
@@ -278,7 +325,11 @@ void attn_bf16_split_kernel(const __bf16* __restrict__ q, __bf16* __restrict__ o
   float* part_l = part_m + kWaves * C::kRows;
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
-    const float l = sum_across_groups(l_run[t]);
+    // the sum of the rounded probabilities, as O adds them up; of the unrounded
+    // ones where the log-sum-exp is written (as in the 256-query kernel)
+    float l = lsum[t][0];
+    if constexpr (kPacked)
+      if (src.lse != nullptr) l = sum_across_groups(l_run[t]);
     const int row = wave * C::kRows + 16 * t + l16;
     if (grp == 0) {
       part_m[row] = m_run[t];

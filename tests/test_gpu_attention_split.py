@@ -95,6 +95,34 @@ def test_packed_with_log_sum_exp(head_dim, grid):
         np.testing.assert_allclose(exact(lse[c * nq:(c + 1) * nq]), want, atol=1e-4)
 
 
+def rounded_like_the_256_query_kernel(q, K, V, scale):
+    """Attention with the probabilities rounded to bf16 relative to the reference that the
+    256-query kernel starts from, the largest score of the first 32 keys, and normalised by
+    their sum (float64 otherwise; the output rounded to bf16)."""
+    out = torch.empty(q.shape, dtype=torch.float64)
+    for h in range(q.shape[1]):
+        s = (q[:, h].double() @ K[:, h].double().T) * (scale / math.log(2.0))
+        p = torch.exp2(s - s[:, :32].max(1, keepdim=True).values).to(torch.bfloat16).double()
+        out[:, h] = (p @ V[:, h].double()) / p.sum(1, keepdim=True)
+    return out.to(torch.bfloat16).float().numpy()
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_probabilities_are_rounded_as_by_the_256_query_kernel(head_dim):
+    # A float32 score is off by a few 2^-24 of its size (up to 10 here), which moves about one
+    # probability in 2000 across a rounding border, by 2^-8 of it: relative-L2 about 1e-4.
+    # Rounded relative to another reference, every probability differs by up to 2^-8: 3e-3.
+    w = small("bf16", head_dim, grid_h=6, grid_w=11, stages=1, layers=1, n_chunks=2)
+    cache, K, V = make_cache(w, 1, 1), [], []
+    for c in range(w.n_chunks):
+        q, k, v = (synth.chunk_tensor(w, t, c, 0, 0) for t in (synth.T_Q, synth.T_K, synth.T_V))
+        out = exact(cache.chunk_attention(0, 0, c, to_dev(q), to_dev(k), to_dev(v)))
+        K, V = K + [k], V + [v]
+        ref = rounded_like_the_256_query_kernel(q, torch.cat(K), torch.cat(V), 1.0 / math.sqrt(head_dim))
+        assert np.linalg.norm(out - ref) <= 5e-4 * np.linalg.norm(ref)
+        cache.kv_publish(0, 0, c, to_dev(k), to_dev(v))
+
+
 @pytest.mark.parametrize("head_dim", [64, 128])
 def test_blocks_of_keys_that_score_minus_infinity(head_dim):
     # products past the float32 range: whole 32-key blocks, the first one of several waves

@@ -80,7 +80,6 @@ constexpr int kWaveQ = 16 * kQH;            // queries per wave
 constexpr int kBlockQ = kWaves * kWaveQ;    // queries per workgroup
 constexpr int kBK = 64;                     // keys per tile
 constexpr int kXcds = 8;
-constexpr int kCus = 256;                   // workgroups of one round (one per CU)
 constexpr float kSumLimit = 16.0f;          // checked pass: largest block sum of probabilities kept
 constexpr float kFastLimit = 0x1p64f;       // fast pass: largest row sum before the checked pass
 // passes of the key loop
@@ -784,7 +783,7 @@ struct SetTiles {
     ++sets;
   }
   double mean() const { return sum / sets; }
-  double whole(unsigned workgroups) const { return fmax(most, mean() * workgroups / kCus); }
+  double whole(unsigned workgroups) const { return fmax(most, mean() * workgroups / device_cus()); }
 };
 
 }  // namespace
@@ -808,8 +807,9 @@ hipError_t launch_attention_bf16(const void* q, void* out, int nq, int heads, in
   const int n_qtiles = (nq + kBlockQ - 1) / kBlockQ;
   const int units = n_qtiles * heads;
   const int n_tail = units - tail.n_full;
-  const double rounds = double((tail.n_full + kCus - 1) / kCus) +
-                        (n_tail > 0 ? double((n_tail * tail.split + kCus - 1) / kCus) / tail.split : 0.0);
+  const int cus = device_cus();
+  const double rounds = double((tail.n_full + cus - 1) / cus) +
+                        (n_tail > 0 ? double((n_tail * tail.split + cus - 1) / cus) / tail.split : 0.0);
   const int tiles = attention_bf16_key_tiles(segs);
   if (const int qt = attention_bf16_split_tiles(nq, heads, head_dim, 1, tiles, tiles, rounds * tiles,
                                                 n_tail > 0))

@@ -406,10 +406,10 @@ int attention_bf16_split_tiles(int nq, int heads, int head_dim, int sets, double
   const Cost two = wide ? Cost{6.5, 0.36} : Cost{5.0, 0.23};
   constexpr double kMerge = 9.0;
   constexpr double kMargin = 0.95;   // near a tie the 256-query kernel, which reads less
-  constexpr int kCus = 256;
+  const int cus = device_cus();
   const auto split_us = [&](int qt, const Cost& c) {
     const int64_t groups = int64_t((nq + 16 * qt - 1) / (16 * qt)) * heads * sets;
-    return c.fixed + c.tile * fmax(tiles_max, tiles_mean * double((groups + kCus - 1) / kCus));
+    return c.fixed + c.tile * fmax(tiles_max, tiles_mean * double((groups + cus - 1) / cus));
   };
   const double t0 = kMargin * (whole.fixed + whole_tiles * whole.tile + (merged ? kMerge : 0.0));
   const double t1 = split_us(1, one), t2 = split_us(2, two);

@@ -798,14 +798,15 @@ SplitChoice choose_split(const PackedPlan& plan, int heads, int head_dim, const 
       sum += tiles * workgroups;
       most = fmax(most, tiles);
     }
-    double us(const Cost& c) const { return c.fixed + c.tile * fmax(most, sum / 256.0 + 0.35 * most); }
+    double us(const Cost& c, int cus) const { return c.fixed + c.tile * fmax(most, sum / cus + 0.35 * most); }
   };
   constexpr double kMargin = 0.92;   // near a tie the 256-row kernels, which read less
   const bool wide = head_dim == 128;
+  const int cus = device_cus();
   const Cost cost_q[3] = {wide ? Cost{4.0, 2.40} : Cost{4.0, 1.60}, wide ? Cost{6.0, 0.43} : Cost{7.0, 0.22},
                           wide ? Cost{7.0, 0.59} : Cost{6.0, 0.32}};
   const Cost cost_k[3] = {wide ? Cost{4.0, 2.70} : Cost{6.0, 1.75}, wide ? Cost{8.0, 0.46} : Cost{8.0, 0.27},
-                          wide ? Cost{8.0, 0.46} : Cost{8.0, 0.32}};
+                          Cost{8.0, 0.32}};   // (two tiles: d = 64 only)
   const int nq = plan.chunk_tokens, n = plan.n_chunks;
   const int window = plan.window < n ? plan.window : n;
   const auto groups = [](int rows, int per) { return double((rows + per - 1) / per); };
@@ -828,7 +829,7 @@ SplitChoice choose_split(const PackedPlan& plan, int heads, int head_dim, const 
       lk.add(tiles, groups(plan.frame_tokens, per) * heads);
     }
     const double margin = t == 0 ? kMargin : 1.0;
-    const double us_q = margin * lq.us(cost_q[t]), us_k = margin * lk.us(cost_k[t]);
+    const double us_q = margin * lq.us(cost_q[t], cus), us_k = margin * lk.us(cost_k[t], cus);
     if (t == 0 || us_q < best_q) {
       best_q = us_q;
       choice.q = t;

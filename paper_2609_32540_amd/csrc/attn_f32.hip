@@ -270,12 +270,13 @@ void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, int n
 }
 
 // Query tiles per workgroup.  Two tiles halve the K and V loads per product;
-// one tile gives twice the workgroups.  A launch takes ceil(workgroups / 256)
+// one tile gives twice the workgroups.  A launch takes ceil(workgroups / CUs)
 // rounds of the GPU (one workgroup per CU), each as long as its tiles, so the
 // form with the shorter sum of rounds is used and two tiles on a tie.
 int query_tiles(int nq, int heads, int sets) {
+  const int cus = device_cus();
   const auto rounds = [&](int qt) {
-    return (int64_t((nq + 16 * qt - 1) / (16 * qt)) * heads * sets + 255) / 256;
+    return (int64_t((nq + 16 * qt - 1) / (16 * qt)) * heads * sets + cus - 1) / cus;
   };
   return 2 * rounds(2) <= rounds(1) ? 2 : 1;
 }

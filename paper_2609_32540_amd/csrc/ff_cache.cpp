@@ -28,6 +28,21 @@
 #include "ff.h"
 #include "ff_internal.h"
 
+// Compute units of the current device (queried once per device; a failed
+// query falls back to 256, which only affects the launch choices).
+int ff::device_cus() {
+  static std::atomic<int> cus[64] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  int n = cus[dev].load(std::memory_order_relaxed);
+  if (n == 0) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+      n = 256;
+    cus[dev].store(n, std::memory_order_relaxed);
+  }
+  return n;
+}
+
 namespace {
 
 thread_local std::string g_last_error;
@@ -196,21 +211,6 @@ ff_status check_aligned(const void* p, const char* name) {
   if (reinterpret_cast<uintptr_t>(p) % 16 != 0)
     return fail(FF_ERR_INVALID_ARG, "%s must be 16-byte aligned", name);
   return FF_OK;
-}
-
-// Compute units of the current device (queried once per device; a failed
-// query falls back to 256, which only affects the tail-split choice).
-int device_cus() {
-  static std::atomic<int> cus[64] = {};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  int n = cus[dev].load(std::memory_order_relaxed);
-  if (n == 0) {
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-      n = 256;
-    cus[dev].store(n, std::memory_order_relaxed);
-  }
-  return n;
 }
 
 // Split of the last round of `units` equal workgroups of n_tiles key tiles
@@ -498,7 +498,7 @@ ff_status chunk_attention_impl(ff_cache* cache, int32_t stage, int32_t layer, in
   if (d.dtype == FF_DT_BF16) {
     const ff::TailSplit tail =
         choose_tail_split(ff::attention_bf16_units(chunk_tokens, heads),
-                          ff::attention_bf16_key_tiles(segs), device_cus(),
+                          ff::attention_bf16_key_tiles(segs), ff::device_cus(),
                           part_slots, part);
     e = ff::launch_attention_bf16(q, out, chunk_tokens, heads, D, softmax_scale, segs, tail,
                                   static_cast<hipStream_t>(stream));

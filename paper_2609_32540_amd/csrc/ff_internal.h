@@ -97,6 +97,10 @@ struct RopeParams {
   int32_t n_th;                       // pairs [n_t, n_th) use the row, the rest the column
 };
 
+// Compute units of the current device, which the launch choices count their
+// rounds of workgroups in.
+int device_cus();
+
 // Copy token-major [n_tok][heads][d] into head-major storage
 // dst + h * dst_head_stride + (dst_tok0 + t) * d, for K and V in one launch.
 hipError_t launch_kv_scatter(const void* k_src, const void* v_src, void* k_dst, void* v_dst,

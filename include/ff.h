@@ -205,7 +205,9 @@ size_t ff_chunk_attention_workspace_bytes(const ff_cache* cache);
  * cache's per-stage scratch region, so calls of one stage (e.g. two layers)
  * may overlap on different streams as long as each has its own workspace.
  * A workspace smaller than ff_chunk_attention_workspace_bytes() only limits
- * the split (results stay within the same bar); NULL runs unsplit.  The
+ * the split (results stay within the same bar); NULL runs unsplit.  (Small
+ * launches split the keys inside each workgroup instead and use no workspace.)
+ * The
  * workspace is the caller's until the call's work on `stream` is done.
  * Everything else as ff_chunk_attention (Sec. 3.1). */
 ff_status ff_chunk_attention_ws(ff_cache* cache, int32_t stage, int32_t layer, int64_t chunk_index,
@@ -249,14 +251,16 @@ typedef struct {
 
 /* The attention of 1 <= n <= FF_MAX_BATCH independent items in one launch,
  * e.g. the stages' forwards of one wavefront round (chunk i at stage s, chunk
- * i-1 at stage s+1, ..): one launch instead of n, which pays for items small
+ * i-1 at stage s+1, ..): one launch instead of n (two where read sets of different
+ * lengths call for different kernels), which pays for items small
  * next to the GPU (far fewer (head, 256-query) units than compute units).
  * Item j computes its ff_chunk_attention(_bank) call's attention (Sec. 3.1 and
  * App. Alg. 1, the Evaluate step of every rank of a round); the batch is
- * never split along keys, so an item is bit-identical to a single call that
- * is not tail-split either, and within the same bf16 bar of the exact result
- * as a single call that is (its partial results are merged in a different
- * order).  Items share
+ * never tail-split and an item's kernel does not depend on the other items, so
+ * an item is bit-identical to a single call that could not be tail-split either
+ * (without a workspace, or of fewer than 16 key tiles of 64), and within the same
+ * bf16 bar of the exact result as one that could (its partial results are
+ * merged in a different order).  Items share
  * softmax_scale; each is validated as its single call would be, all before
  * anything is enqueued.  Items may read the same ring; their outputs must not
  * overlap each other or any input. */

@@ -786,6 +786,33 @@ struct SetTiles {
   double whole(unsigned workgroups) const { return fmax(most, mean() * workgroups / device_cus()); }
 };
 
+// Query tiles of the key-split kernel for a single call of `tiles` key tiles with
+// the given tail split, 0 where the 256-query kernel is the faster one.
+int single_split_tiles(int nq, int heads, int head_dim, int tiles, int n_full, int split) {
+  const int cus = device_cus(), n_tail = attention_bf16_units(nq, heads) - n_full;
+  const double rounds = double((n_full + cus - 1) / cus) +
+                        (n_tail > 0 ? double((n_tail * split + cus - 1) / cus) / split : 0.0);
+  return attention_bf16_split_tiles(nq, heads, head_dim, 1, tiles, tiles, rounds * tiles, n_tail > 0);
+}
+
+// Whether a batch item runs on the key-split kernel, and with it a single call that
+// is not tail-split: where that is the faster form of a single call (against the
+// 256-query kernel with the tail split a cache's own scratch allows) and of a batch
+// of kMaxBatch such items.  The answer hangs on the shape and this read set only, not
+// on the other items, so an item has the bits of its single call.  Of random calls
+// of 1 to 40 heads x 50 to 18000 queries, 1.4% stay on the 256-query kernel where a
+// single call alone would gain (by the estimates 1.3 to 2.3 times: 24 heads x 64, 741
+// queries over 12 tiles); a batch on the key-split kernel wherever a single call
+// gains would lose up to twice its time in 8%.
+bool item_key_split(int nq, int heads, int head_dim, int tiles) {
+  const int units = attention_bf16_units(nq, heads), cus = device_cus();
+  const int parts = tail_parts(units, tiles, cus, kMaxTailSplit * (units < kTailUnits ? units : kTailUnits));
+  if (!single_split_tiles(nq, heads, head_dim, tiles, parts > 1 ? units - units % cus : units, parts))
+    return false;
+  const double batch_tiles = fmax(tiles, double(tiles) * kMaxBatch * units / cus);
+  return attention_bf16_split_tiles(nq, heads, head_dim, kMaxBatch, tiles, tiles, batch_tiles, false) != 0;
+}
+
 }  // namespace
 
 int attention_bf16_units(int nq, int heads) { return heads * ((nq + kBlockQ - 1) / kBlockQ); }
@@ -807,13 +834,14 @@ hipError_t launch_attention_bf16(const void* q, void* out, int nq, int heads, in
   const int n_qtiles = (nq + kBlockQ - 1) / kBlockQ;
   const int units = n_qtiles * heads;
   const int n_tail = units - tail.n_full;
-  const int cus = device_cus();
-  const double rounds = double((tail.n_full + cus - 1) / cus) +
-                        (n_tail > 0 ? double((n_tail * tail.split + cus - 1) / cus) / tail.split : 0.0);
   const int tiles = attention_bf16_key_tiles(segs);
-  if (const int qt = attention_bf16_split_tiles(nq, heads, head_dim, 1, tiles, tiles, rounds * tiles,
-                                                n_tail > 0))
-    return launch_attention_bf16_split(qt, q, out, nq, heads, head_dim, softmax_scale, segs, stream);
+  int split_tiles = 0;
+  if (tail.split > 1)
+    split_tiles = single_split_tiles(nq, heads, head_dim, tiles, tail.n_full, tail.split);
+  else if (item_key_split(nq, heads, head_dim, tiles))
+    split_tiles = attention_bf16_split_tiles(nq, heads, head_dim, 1, tiles, tiles, INFINITY, false);
+  if (split_tiles)
+    return launch_attention_bf16_split(split_tiles, q, out, nq, heads, head_dim, softmax_scale, segs, stream);
   const dim3 grid(tail.n_full + n_tail * tail.split);
   const float scale_log2 = float(double(softmax_scale) * 1.4426950408889634);
   if (head_dim == 128)
@@ -841,20 +869,31 @@ hipError_t launch_attention_bf16_batch(int nq, int heads, int head_dim, float so
                                        const KvBatch& b, hipStream_t stream) {
   if (nq <= 0 || b.n <= 0) return hipSuccess;
   const int n_qtiles = (nq + kBlockQ - 1) / kBlockQ;
-  const dim3 grid(b.n * n_qtiles * heads);
+  KvBatch whole_b = {}, split_b = {};   // the items of each kernel
   SetTiles t;
-  for (int j = 0; j < b.n; ++j) t.add(attention_bf16_key_tiles(b.set[j]));
-  if (const int qt = attention_bf16_split_tiles(nq, heads, head_dim, b.n, t.mean(), t.most,
-                                                t.whole(grid.x), false))
-    return launch_attention_bf16_split_batch(qt, nq, heads, head_dim, softmax_scale, b, stream);
+  for (int j = 0; j < b.n; ++j) {
+    const int tiles = attention_bf16_key_tiles(b.set[j]);
+    const bool split = item_key_split(nq, heads, head_dim, tiles);
+    if (split) t.add(tiles);
+    KvBatch& p = split ? split_b : whole_b;
+    p.set[p.n] = b.set[j];
+    p.q[p.n] = b.q[j];
+    p.out[p.n++] = b.out[j];
+  }
+  if (split_b.n > 0) {
+    const int qt = attention_bf16_split_tiles(nq, heads, head_dim, split_b.n, t.mean(), t.most, INFINITY, false);
+    const hipError_t e = launch_attention_bf16_split_batch(qt, nq, heads, head_dim, softmax_scale, split_b, stream);
+    if (e != hipSuccess || whole_b.n == 0) return e;
+  }
+  const dim3 grid(whole_b.n * n_qtiles * heads);
   const float scale_log2 = float(double(softmax_scale) * 1.4426950408889634);
   const TailSplit whole = {int(grid.x), 1, nullptr};
   if (head_dim == 128)
     hipLaunchKernelGGL((attn_bf16_kernel<128, KvBatch>), grid, dim3(kThreads), 0, stream,
-                       nullptr, nullptr, nq, heads, scale_log2, b, n_qtiles, whole);
+                       nullptr, nullptr, nq, heads, scale_log2, whole_b, n_qtiles, whole);
   else
     hipLaunchKernelGGL((attn_bf16_kernel<64, KvBatch>), grid, dim3(kThreads), 0, stream,
-                       nullptr, nullptr, nq, heads, scale_log2, b, n_qtiles, whole);
+                       nullptr, nullptr, nq, heads, scale_log2, whole_b, n_qtiles, whole);
   return hipGetLastError();
 }
 

@@ -95,11 +95,6 @@ struct Layout {
   size_t total;
 };
 
-// Tail split: at most this many key parts per unit, and partial slots for up
-// to kTailUnits units (one round of workgroups on a 256-CU device).
-constexpr int kMaxTailSplit = 4;
-constexpr int kTailUnits = 256;
-
 // The descriptor as the cache uses it: all-zero rope pairs select the split of
 // the Wan2.1 backbone, d/2 - 2 floor(d/6) pairs on t and floor(d/6) on each of
 // h and w ((22, 21, 21) at d = 128, (12, 10, 10) at d = 64).
@@ -160,7 +155,7 @@ Layout make_layout(const ff_cache_desc* d) {
   L.tail_stage_bytes = 0;
   if (d->dtype == FF_DT_BF16) {
     const int units = ff::attention_bf16_units(int(L.chunk_tokens), d->num_heads);
-    L.tail_slots = kMaxTailSplit * std::min(units, kTailUnits);
+    L.tail_slots = ff::kMaxTailSplit * std::min(units, ff::kTailUnits);
     L.tail_stage_bytes = align_up(size_t(L.tail_slots) * ff::attention_bf16_part_bytes(d->head_dim));
   }
   L.total = L.tail_base + L.tail_stage_bytes * d->num_stages;
@@ -213,25 +208,10 @@ ff_status check_aligned(const void* p, const char* name) {
   return FF_OK;
 }
 
-// Split of the last round of `units` equal workgroups of n_tiles key tiles
-// each over `cus` compute units: the units of the partial round run as up
-// to kMaxTailSplit key parts (at least 8 tiles each) when that shortens the
-// round, estimated as ceil(parts / cus) / split of a whole workgroup.
+// Split of the last, partial round of `units` workgroups (no scratch: none).
 ff::TailSplit choose_tail_split(int units, int n_tiles, int cus, int slots, float* part) {
-  ff::TailSplit t = {units, 1, part};
-  const int n_tail = units % cus;
-  if (n_tail == 0 || part == nullptr) return t;
-  double best = 1.0;
-  for (int s = 2; s <= kMaxTailSplit; ++s) {
-    if (n_tiles < 8 * s || n_tail * s > slots) break;
-    const double cost = double((n_tail * s + cus - 1) / cus) / s;
-    if (cost < best - 1e-9) {
-      best = cost;
-      t.split = s;
-    }
-  }
-  if (t.split > 1) t.n_full = units - n_tail;
-  return t;
+  const int split = part ? ff::tail_parts(units, n_tiles, cus, slots) : 1;
+  return {split > 1 ? units - units % cus : units, split, part};
 }
 
 ff_status hip_status(hipError_t e, const char* what) {

@@ -127,6 +127,29 @@ struct TailSplit {
   float* part;
 };
 
+// At most this many key parts per unit; a cache's scratch holds partials for up
+// to kTailUnits units (one round of workgroups on a 256-CU device) per stage.
+constexpr int kMaxTailSplit = 4;
+constexpr int kTailUnits = 256;
+
+// Key parts per unit of the last round of `units` equal workgroups of n_tiles key
+// tiles each over `cus` compute units (1: no split), with room for `slots` partials:
+// at least 8 tiles per part, the fewest rounds the parts add up to.
+inline int tail_parts(int units, int n_tiles, int cus, int slots) {
+  const int n_tail = units % cus;
+  int parts = 1;
+  double best = 1.0;
+  for (int s = 2; n_tail > 0 && s <= kMaxTailSplit; ++s) {
+    if (n_tiles < 8 * s || n_tail * s > slots) break;
+    const double cost = double((n_tail * s + cus - 1) / cus) / s;
+    if (cost < best - 1e-9) {
+      best = cost;
+      parts = s;
+    }
+  }
+  return parts;
+}
+
 // Units (head, 256-query tile) of one launch and the bytes of one partial.
 int attention_bf16_units(int nq, int heads);
 // Key tiles a workgroup of the bf16 kernel walks over the read set segs.
@@ -141,7 +164,8 @@ hipError_t launch_attention_f32(const void* q, void* out, int nq, int heads, int
                                 float softmax_scale, const KvSegments& segs,
                                 hipStream_t stream);
 
-// Batched launches: item j of b reads b.set[j]; no tail split.
+// Batched launches: item j of b reads b.set[j]; no tail split.  bf16 items whose
+// read sets lie on both sides of the line to the key-split kernel take two launches.
 hipError_t launch_attention_bf16_batch(int nq, int heads, int head_dim, float softmax_scale,
                                        const KvBatch& b, hipStream_t stream);
 
@@ -163,8 +187,8 @@ hipError_t launch_attention_f32_packed(const void* q, void* out, int heads, int 
 // 256-query workgroups.  Returns the 16-query tiles per workgroup to launch them
 // with, or 0 where the 256-query kernel is the better one.  tiles_mean and
 // tiles_max: 64-key tiles of the launch's read sets; whole_tiles: the tiles that
-// the busiest CU would walk in the 256-query kernel; merged: whether that would
-// need the merge kernel.
+// the busiest CU would walk in the 256-query kernel (INFINITY: never 0); merged:
+// whether that would need the merge kernel.
 int attention_bf16_split_tiles(int nq, int heads, int head_dim, int sets, double tiles_mean,
                                double tiles_max, double whole_tiles, bool merged);
 

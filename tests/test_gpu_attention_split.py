@@ -73,6 +73,39 @@ def test_batch_items_of_different_lengths(head_dim):
         check_attention(exact(out), ref, "bf16", f"stage {s}")
 
 
+# An item has the bits of its single call without a workspace whatever the other items are,
+# also where the two launches would do best with different forms: 16 queries a workgroup alone
+# and 32 in a batch of four (6 heads x 351 queries over 1053 keys, 12 x 198 over 1024, 24 x 198
+# at d = 64); the key-split kernel alone and the 256-query one in a batch (24 x 351, 40 x 198,
+# 12 x 1170); items on both sides of the line in one batch (38 x 198 at d = 64: 4 key tiles
+# against 8 and 12).  With scratch too where there are fewer than 16 key tiles.
+@pytest.mark.parametrize("heads,grid,head_dim,W", [(6, (9, 13), 128, 2), (12, (6, 11), 128, 3),
+                                                   (24, (6, 11), 64, 2), (24, (9, 13), 128, 2),
+                                                   (40, (6, 11), 128, 1), (12, (15, 26), 128, 3),
+                                                   (12, (15, 26), 64, 3), (38, (6, 11), 64, 2)])
+def test_batch_items_have_the_bits_of_their_single_calls(heads, grid, head_dim, W):
+    S = 4
+    w = small("bf16", head_dim, heads=heads, grid_h=grid[0], grid_w=grid[1], ring_chunks=W, stages=S,
+              layers=1, n_chunks=W + 1)
+    cache, g = make_cache(w, S, 1), torch.Generator(device="cuda").manual_seed(heads)
+    rnd = lambda: torch.randn((w.chunk_tokens, heads, head_dim), generator=g, device="cuda").to(torch.bfloat16)
+    items = []
+    for s in range(S):      # stage 0 holds no chunk, stage 3 a full ring
+        n = s * W // (S - 1)
+        for c in range(n):
+            cache.kv_publish(s, 0, c, rnd(), rnd())
+        items.append(dict(stage=s, layer=0, chunk=n, q=rnd(), k=rnd(), v=rnd()))
+    singles = [cache.chunk_attention_ws(it["stage"], 0, it["chunk"], it["q"], it["k"], it["v"], None)
+               for it in items]
+    for it, one in zip(items, singles):
+        if (it["chunk"] + 1) * -(-w.chunk_tokens // 64) < 16:
+            assert torch.equal(one, cache.chunk_attention(it["stage"], 0, it["chunk"], it["q"], it["k"], it["v"]))
+    for pick in ([0, 1, 2, 3], [0, 3], [2], [1, 1, 1]):
+        outs = cache.chunk_attention_batch([dict(items[j], out=torch.empty_like(items[j]["q"])) for j in pick])
+        for j, out in zip(pick, outs):
+            assert torch.equal(out, singles[j]), (pick, j)
+
+
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("grid", [(1, 1), (3, 5), (5, 7)])
 def test_packed_with_log_sum_exp(head_dim, grid):

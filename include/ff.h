@@ -207,8 +207,7 @@ size_t ff_chunk_attention_workspace_bytes(const ff_cache* cache);
  * A workspace smaller than ff_chunk_attention_workspace_bytes() only limits
  * the split (results stay within the same bar); NULL runs unsplit.  (Small
  * launches split the keys inside each workgroup instead and use no workspace.)
- * The
- * workspace is the caller's until the call's work on `stream` is done.
+ * The workspace is the caller's until the call's work on `stream` is done.
  * Everything else as ff_chunk_attention (Sec. 3.1). */
 ff_status ff_chunk_attention_ws(ff_cache* cache, int32_t stage, int32_t layer, int64_t chunk_index,
                                 const void* q, const void* k_cur, const void* v_cur, void* out,

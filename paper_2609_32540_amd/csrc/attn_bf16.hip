@@ -843,6 +843,8 @@ hipError_t launch_attention_bf16(const void* q, void* out, int nq, int heads, in
   if (split_tiles)
     return launch_attention_bf16_split(split_tiles, q, out, nq, heads, head_dim, softmax_scale, segs, stream);
   const dim3 grid(tail.n_full + n_tail * tail.split);
+  last_launch.query_tiles = 0;
+  last_launch.key_parts = tail.split;
   const float scale_log2 = float(double(softmax_scale) * 1.4426950408889634);
   if (head_dim == 128)
     hipLaunchKernelGGL((attn_bf16_kernel<128, KvSegments>), grid, dim3(kThreads), 0, stream,
@@ -886,6 +888,8 @@ hipError_t launch_attention_bf16_batch(int nq, int heads, int head_dim, float so
     if (e != hipSuccess || whole_b.n == 0) return e;
   }
   const dim3 grid(whole_b.n * n_qtiles * heads);
+  last_launch.query_tiles = 0;
+  last_launch.key_parts = 1;
   const float scale_log2 = float(double(softmax_scale) * 1.4426950408889634);
   const TailSplit whole = {int(grid.x), 1, nullptr};
   if (head_dim == 128)
@@ -914,6 +918,8 @@ hipError_t launch_attention_bf16_packed(const void* q, void* out, int heads, int
   if (const int qt = attention_bf16_split_tiles(nq, heads, head_dim, plan.n_chunks, t.mean(), t.most,
                                                 t.whole(grid.x), false))
     return launch_attention_bf16_split_packed(qt, q, out, heads, head_dim, softmax_scale, plan, stream);
+  last_launch.query_tiles = 0;
+  last_launch.key_parts = 1;
   const float scale_log2 = float(double(softmax_scale) * 1.4426950408889634);
   const TailSplit whole = {int(grid.x), 1, nullptr};
   if (head_dim == 128)

@@ -377,6 +377,8 @@ hipError_t launch(int qt, const void* q, void* out, int nq, int heads, int head_
   const float c = float(double(softmax_scale) * 1.4426950408889634);
   const int n_qtiles = (nq + 16 * qt - 1) / (16 * qt);
   const dim3 grid(unsigned(n_qtiles * heads * sets));
+  last_launch.query_tiles = qt;
+  last_launch.key_parts = 1;
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, static_cast<const __bf16*>(q),
                        static_cast<__bf16*>(out), nq, heads, c, src, n_qtiles);

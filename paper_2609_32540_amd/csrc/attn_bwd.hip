@@ -879,10 +879,13 @@ hipError_t launch_attention_bwd_bf16(const void* q, const void* out, const void*
   __bf16 *dkp = static_cast<__bf16*>(dk), *dvp = static_cast<__bf16*>(dv);
   __bf16 *dakp = static_cast<__bf16*>(dak), *davp = static_cast<__bf16*>(dav);
   const SplitChoice split = choose_split(plan, heads, head_dim, ku);
-  // Rings (LDS: 160 KB per workgroup): d = 128 dQ fits three 32 KB slots beside its 64 KB
-  // dO stash; the d = 128 dK/dV pass (V stash plus the streamed vectors) four slots of
-  // 32-row tiles, which also keeps the per-block registers within two waves per SIMD
-  // beside both accumulators; d = 64 takes four 64-row slots in both passes.
+  last_launch.bwd_q_tiles = split.q;
+  last_launch.bwd_k_tiles = split.k;
+  // Rings (LDS: 160 KB per workgroup): five slots each.  dQ: 64-row tiles of K and V, 32 KB a
+  // slot at d = 128 (all of the LDS; Q and dO are in registers), 16 KB at d = 64.  dK and dV:
+  // 64 KB of V beside slots of 16.25 KB at d = 128 (32-row tiles of Q and dO with their L and
+  // D, which also keeps the per-block registers within two waves per SIMD beside both
+  // accumulators), 32 KB beside 16.5 KB at d = 64 (64-row tiles).
   if (split.q) {
     const hipError_t e = launch_bwd_split_dq(split.q, q, dout, lse, delta, dq, heads, head_dim,
                                              softmax_scale, plan, stream);

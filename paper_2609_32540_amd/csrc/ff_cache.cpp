@@ -43,6 +43,14 @@ int ff::device_cus() {
   return n;
 }
 
+thread_local ff::LaunchForms ff::last_launch = {};
+
+extern "C" int32_t ff_internal_last_launch(int32_t field) {
+  const ff::LaunchForms& f = ff::last_launch;
+  const int32_t v[4] = {f.query_tiles, f.key_parts, f.bwd_q_tiles, f.bwd_k_tiles};
+  return field >= 0 && field < 4 ? v[field] : -1;
+}
+
 namespace {
 
 thread_local std::string g_last_error;

@@ -97,6 +97,17 @@ struct RopeParams {
   int32_t n_th;                       // pairs [n_t, n_th) use the row, the rest the column
 };
 
+// The forms that the calling thread's last attention and packed backward launches
+// took, so that a test can tell that it reached the one it is about (exported as
+// ff_internal_last_launch, not part of the C ABI).
+struct LaunchForms {
+  int32_t query_tiles;   // 16-query tiles per workgroup of the key-split kernel; 0: the 256-query kernel
+  int32_t key_parts;     // key parts per unit of the tail split; 1: none
+  int32_t bwd_q_tiles;   // 16-row tiles per workgroup of the split dQ kernel; 0: the 256-row kernel
+  int32_t bwd_k_tiles;   // the same of dK and dV
+};
+extern thread_local LaunchForms last_launch;
+
 // Compute units of the current device, which the launch choices count their
 // rounds of workgroups in.
 int device_cus();

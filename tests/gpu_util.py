@@ -3,7 +3,7 @@ oracle's cache for one workload, move seeded inputs, compare results."""
 from __future__ import annotations
 
 import math
-from typing import Dict, List, Optional, Sequence, Tuple
+from typing import Dict, List, NamedTuple, Optional, Sequence, Tuple
 
 import numpy as np
 import torch
@@ -43,6 +43,18 @@ def make_oracle(w: synth.Workload, stages: Optional[int] = None,
                 layers: Optional[int] = None) -> fo.RendererCacheOracle:
     return fo.RendererCacheOracle(stages=stages or w.stages, layers=layers or w.layers,
                                   W=w.ring_chunks)
+
+
+class LaunchForms(NamedTuple):
+    query_tiles: int     # attention: 16-query tiles per workgroup of the key-split kernel, 0: 256-query kernel
+    key_parts: int       # attention: key parts per unit of the tail split
+    bwd_q_tiles: int     # backward: 16-row tiles per workgroup of the split dQ kernel, 0: 256-row kernel
+    bwd_k_tiles: int     # the same of dK and dV
+
+
+def last_launch() -> LaunchForms:
+    """The forms this thread's last attention and packed backward launches took."""
+    return LaunchForms(*(ff.lib().ff_internal_last_launch(i) for i in range(4)))
 
 
 def exact(t: torch.Tensor) -> np.ndarray:

@@ -37,7 +37,7 @@ def test_tiles_and_blocks(head_dim, heads, grid):
 
 @pytest.mark.parametrize("head_dim", [64, 128])
 def test_batch_equals_single_calls(head_dim):
-    # the same kernel and query tiling: bit-identical while both launches pick one tile
+    # bit-identical: a query's sums do not depend on the query tiles of its workgroup
     w = small("f32", head_dim, grid_h=5, grid_w=7, stages=3, layers=1, n_chunks=3)
     cache, oracle = make_cache(w, 3, 1), make_oracle(w, 3, 1)
     for c in range(w.n_chunks):

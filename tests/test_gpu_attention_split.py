@@ -14,7 +14,7 @@ import synth
 from oracle import ff_oracle as fo
 from paper_2609_32540_amd import ff
 
-from gpu_util import PairedRun, check_attention, exact, make_cache, make_oracle, to_dev
+from gpu_util import PairedRun, check_attention, exact, last_launch, make_cache, make_oracle, to_dev
 from test_gpu_packed import clip, oracle_packed
 from test_gpu_parity import small
 
@@ -29,7 +29,8 @@ def _needs_gpu():
 
 
 # chunk tokens 3, 15, 18, 33 and 99 (16-query workgroups), and 351 with 24 heads (528
-# workgroups of one tile are three rounds: two tiles a workgroup, the last ragged)
+# workgroups of one tile are three rounds: two tiles a workgroup, the last ragged, from 16 key
+# tiles on, at d = 64 from 22; its first call, of 10, is left to the 256-query kernel)
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("heads,grid", [(1, (1, 1)), (2, (1, 5)), (2, (2, 3)), (3, (1, 11)), (3, (3, 11)),
                                         (24, (9, 13))])
@@ -39,6 +40,7 @@ def test_tiles_and_blocks(head_dim, heads, grid):
     run = PairedRun(w, rope=False)
     for c in range(w.n_chunks):
         run.step(c, 0, 0)
+        assert last_launch().query_tiles == (1 if heads < 24 else [0, 2 if head_dim == 128 else 1, 2, 2][c])
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
@@ -68,7 +70,9 @@ def test_batch_items_of_different_lengths(head_dim):
                 cache.kv_publish(s, 0, c, k, v)
                 oracle.publish(s, 0, c, exact(k), exact(v))
         items.append(dict(stage=s, layer=0, chunk=s, q=q, k=k, v=v))
-    for s, (it, out) in enumerate(zip(items, cache.chunk_attention_batch(items))):
+    outs = cache.chunk_attention_batch(items)
+    assert last_launch().query_tiles == 1
+    for s, (it, out) in enumerate(zip(items, outs)):
         ref = oracle.attention(s, 0, s, exact(it["q"]), exact(it["k"]), exact(it["v"]))
         check_attention(exact(out), ref, "bf16", f"stage {s}")
 
@@ -118,6 +122,7 @@ def test_packed_with_log_sum_exp(head_dim, grid):
     scale = 1.0 / math.sqrt(head_dim)
     out = ff.packed_attention(q, k, v, n_chunks=n, window=1, anchor_k=ak, anchor_v=av, frame_tokens=G,
                               anchors_of_chunk=table, lse=lse)
+    assert last_launch().query_tiles == 1
     ref = oracle_packed(w, q, k, v, ak, av, table, 1, scale)
     nq = w.chunk_tokens
     for c in range(n):
@@ -173,15 +178,17 @@ def test_blocks_of_keys_that_score_minus_infinity(head_dim):
         check_attention(exact(out), oracle.attention(0, 0, 0, exact(q), exact(kk), exact(v)), "bf16")
 
 
-# the smallest launches left to the 256-query kernel, whose partial last round runs as 2, 3
-# and 4 key parts: 96, 80 and 60 units on 256 CUs
-@pytest.mark.parametrize("heads,grid,head_dim", [(24, (12, 22), 128), (24, (12, 22), 64),
-                                                 (40, (9, 13), 128), (12, (15, 26), 128),
-                                                 (12, (15, 26), 64)])
-def test_key_parts_of_the_256_query_kernel(heads, grid, head_dim):
+# launches left to the 256-query kernel, whose partial last round runs as 2, 3 and 4 key parts:
+# 96, 80 and 60 units on 256 CUs
+@pytest.mark.parametrize("heads,grid,head_dim,parts", [(24, (12, 22), 128, 2), (24, (12, 22), 64, 2),
+                                                       (16, (15, 26), 128, 3), (12, (15, 26), 128, 4),
+                                                       (12, (15, 26), 64, 4)])
+def test_key_parts_of_the_256_query_kernel(heads, grid, head_dim, parts):
     w = small("bf16", head_dim, heads=heads, grid_h=grid[0], grid_w=grid[1], ring_chunks=5, stages=1,
               layers=1, n_chunks=6)
     run = PairedRun(w, rope=False)
     rows = np.r_[0:40, w.chunk_tokens - 40:w.chunk_tokens]
     for c in range(w.n_chunks):
         run.step(c, 0, 0, check=c >= 4, heads=[0, heads - 1], rows=rows)
+        if c >= 4:
+            assert last_launch()[:2] == (0, parts)

@@ -158,9 +158,10 @@ def test_packed_log_sum_exp_reference_far_below_the_max(d):
     chunk's first block sets a reference far below its largest scores: chunk 0's
     keys are tiny and the first block of every chunk's read set is chunk 0's;
     keys scaled by 8 give probabilities up to ~2^35 relative to that reference,
-    keys scaled by 24 push row sums past 2^64, so the units of chunks 3 and 4
-    run the checked pass after the fast one.  Output and base-2 log-sum-exp
-    against the oracle (log2_sum_exp2 over the packed mask)."""
+    keys scaled by 24 go past 2^56, where the key-split kernel, which this small
+    launch runs, raises its reference (the 256-query kernel's checked pass:
+    test_gpu_256_row_kernels.py).  Output and base-2 log-sum-exp against the
+    oracle (log2_sum_exp2 over the packed mask)."""
     n, W = 5, 4
     w = small("bf16", d, grid=(6, 11), ring_chunks=W, n_chunks=n)
     q, k, v = clip(w, n)

@@ -223,13 +223,12 @@ def test_attention_one_token_chunks(dtype, head_dim):
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("grid", [(6, 11), (12, 22)])
 def test_attention_tail_split_into_key_parts(head_dim, grid):
-    # Fewer (head, 256-query) units than compute units: the whole launch is
-    # the partial last round, run as 2, 3 or 4 key parts (at least 8 key
-    # tiles of 64 each) plus the merge.  6x11 grid: 198-token chunks, one
-    # ragged query tile; anchors 4 tiles + 4 per chunk, so chunks 2..7 see 16,
-    # 20, 24, 28, 32, 32 tiles (2, 2, 3, 3, 4, 4 parts) with part boundaries
-    # inside segments.  12x22 grid: 792-token chunks = 4 query tiles (last
-    # holds 24 queries), 13 tiles per frame group, up to 104 tiles.
+    # Launches far smaller than the GPU over 8 to 104 key tiles, which the
+    # key-split kernel runs: its waves' 32-key blocks end inside segments.  6x11
+    # grid: 198-token chunks (12 tiles of 16 queries, one ragged); anchors 4 tiles
+    # of 64 keys + 4 per chunk.  12x22 grid: 792-token chunks, 13 tiles per frame
+    # group.  (Key parts of the 256-query kernel need larger launches:
+    # test_gpu_attention_split.py and test_gpu_256_row_kernels.py.)
     w = small("bf16", head_dim, heads=2, grid_h=grid[0], grid_w=grid[1], ring_chunks=6,
               stages=1, layers=1, n_chunks=8, anchor_rule="fixed:0,7,20", max_anchor_frames=3)
     run = PairedRun(w, rope=False)
@@ -273,9 +272,9 @@ def test_attention_maximum_segments(dtype, head_dim, grid):
 @pytest.mark.parametrize("head_dim,heads,grid", [(128, 3, (6, 11)), (64, 2, (12, 22))])
 def test_attention_running_max_rescales(head_dim, heads, grid):
     # Keys of later chunks scaled by 1, 3, 9, 27, ..: each new segment carries
-    # logits far above the running max (the rescale path runs again and again,
-    # also inside tail-split key parts), then a chunk whose own keys are tiny
-    # (no rescale, probabilities underflow to 0 for most keys).
+    # logits far above the running max (the key-split kernel raises its reference
+    # again and again), then a chunk whose own keys are tiny (no rescale,
+    # probabilities underflow to 0 for most keys).
     W = 4
     w = small("bf16", head_dim, heads=heads, grid_h=grid[0], grid_w=grid[1], ring_chunks=W,
               stages=1, layers=1, n_chunks=7, anchor_rule="none", max_anchor_frames=1)
@@ -301,8 +300,9 @@ def test_attention_reference_far_below_the_max(head_dim):
     # (its oldest history chunk, or itself for chunk 0) gives a reference max
     # near 0 while the largest scores sit far above it: keys scaled by 8 give
     # probabilities up to ~2^35 relative to that reference (strongly peaked
-    # rows, no overflow), keys scaled by 24 go past 2^64 (the workgroup's unit
-    # runs again with the reference raised per block).
+    # rows, no overflow), keys scaled by 24 go past 2^56 (the key-split kernel
+    # raises its reference; the 256-query kernel's checked pass is tested in
+    # test_gpu_256_row_kernels.py).
     W = 4
     w = small("bf16", head_dim, heads=2, grid_h=6, grid_w=11, ring_chunks=W,
               stages=1, layers=1, n_chunks=5, anchor_rule="none", max_anchor_frames=1)
@@ -325,8 +325,9 @@ def test_attention_reference_far_below_the_max(head_dim):
 def test_attention_batch_equals_single_calls(dtype, head_dim):
     # the rounds of a 4-stage wavefront (round n: chunk n - s at stage s), each
     # round's attention as one ff_chunk_attention_batch; stage 3 reads its anchors
-    # from a bank.  Bit-identical to the single calls (the batch is never split
-    # along keys, and no single call here is), and within the bar of the oracle.
+    # from a bank.  Bit-identical to the single calls (no launch here is tail-split,
+    # and an item's kernel does not depend on the other items), and within the bar
+    # of the oracle.
     S = 4
     w = small(dtype, head_dim, heads=3, ring_chunks=2, stages=S, layers=1, n_chunks=5,
               anchor_rule="fixed:0,7", max_anchor_frames=2)

@@ -73,9 +73,7 @@ def make_stub(cache, w, X, layers, bank=None):
     return forward
 
 
-# W = 4 gives read sets of up to 23 key tiles: the attention's tail split runs (two key
-# parts per unit) with each stage's partials in its own scratch while the stages run
-# concurrently
+# (launches with concurrent tail splits are larger: test_gpu_256_row_kernels.py)
 @pytest.mark.parametrize("N_R,layers,W", [(6, 2, 2), (3, 1, 2), (7, 1, 4)])
 def test_wavefront_equals_chunk_major(N_R, layers, W):
     S = len(SIGMAS) - 1

@@ -1,5 +1,6 @@
 """Concurrent calls of one stage with caller workspaces (ff_chunk_attention_ws),
-and batch items beside tail-split single calls, against the oracle.
+and batch items beside single calls, against the oracle, at a size whose calls may
+take a workspace and do not write to it.
 
 The renderer attention of Sec. 3.1 is the same whatever scratch memory the
 launch uses: a workspace only moves the fp32 partial results of the key parts
@@ -21,8 +22,9 @@ pytestmark = pytest.mark.gpu
 
 
 def _workload(layers=2, stages=1, head_dim=128):
-    # 6x11 grid, 2 heads: 2 units on a 256-CU part, so every launch is the
-    # partial last round and runs as 2-4 key parts (16 .. 32 key tiles)
+    # 6x11 grid, 2 heads: small launches, which split their keys inside each
+    # workgroup and use no scratch.  (Calls that do use it are larger: the
+    # workspace tests of test_gpu_256_row_kernels.py.)
     return small("bf16", head_dim, heads=2, grid_h=6, grid_w=11, ring_chunks=6, stages=stages,
                  layers=layers, n_chunks=8, anchor_rule="fixed:0,7,20", max_anchor_frames=3)
 
@@ -91,9 +93,9 @@ def test_workspace_sizes_only_limit_the_split():
 
 @pytest.mark.parametrize("head_dim", [128, 64])
 def test_batch_items_beside_tail_split_single_calls(head_dim):
-    # The single calls here are tail-split (2 units on 256 CUs), the batch never
-    # is: an item and its single call may differ in low bits, and both stay
-    # within the bf16 bar of the oracle (App. Alg. 1: one round's forwards).
+    # Small calls, alone and in a batch (single calls with key parts beside a batch
+    # are in test_gpu_256_row_kernels.py): both stay within the bf16 bar of the
+    # oracle (App. Alg. 1: one round's forwards).
     S = 2
     w = _workload(layers=1, stages=S, head_dim=head_dim)
     single, batched = make_cache(w, S, 1), make_cache(w, S, 1)

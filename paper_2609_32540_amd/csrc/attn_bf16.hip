@@ -544,9 +544,15 @@ void attn_bf16_kernel(const __bf16* __restrict__ q, __bf16* __restrict__ out, in
       }
     // A wave without queries (a ragged last tile) has a loop of its own with the
     // copies and barriers of the one below and no products: the unit is done
-    // sooner and draws less power (step of 12 heads x 4680 queries 686 -> 674 us, 40 x
-    // 10800 11.67 -> 11.58 ms, batch of four 12 x 1170 187 -> 180 us; a branch around
-    // the steps of the loop below costs more than it saves).
+    // sooner and draws less power.  Medians of launches alternating with the kernel
+    // without it: batch of four 12 heads x 1170 queries 201 -> 192 us, 12 x 4680 713
+    // -> 696 on one box and 704 -> 703 on another, 40 x 4680 2304 -> 2283; 5 x 10800
+    // and 40 x 10800 within the spread of one side.  (A branch around the steps of
+    // the loop below costs more than it saves.)  In launches of several rounds the
+    // tiles after a short one run out of step with their XCD's others and read part
+    // of K and V again, 5.0 instead of 3.3 GB at 40 x 10800; with this loop in
+    // launches of one round only (a condition on the grid) the large ones took 1.6
+    // to 2% longer, since the condition reaches into the main loop's schedule.
     if (idle) {
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();

@@ -398,7 +398,8 @@ hipError_t launch(int qt, const void* q, void* out, int nq, int heads, int head_
 // (us): 2 heads x 198 queries x 1188 keys 24.5 against 9.4 (QT 1) and 12.5 (QT
 // 2) at d = 128; 12 x 351 x 2106 29.4 / 24.4 / 17.0; 12 x 1170 x 7020 65 / 129 /
 // 83, where every CU has work and the copies (each workgroup its own K and V)
-// bound this kernel.
+// bound this kernel.  (Taken before the waves shared a reference max, which adds
+// about 1 us to each form of it: less than the fits' scatter.)
 int attention_bf16_split_tiles(int nq, int heads, int head_dim, int sets, double tiles_mean,
                                double tiles_max, double whole_tiles, bool merged) {
   struct Cost { double fixed, tile; };   // us, us per tile

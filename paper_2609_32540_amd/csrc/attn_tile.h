@@ -1,4 +1,4 @@
-// Device helpers shared by the bf16 attention kernels.
+// Device helpers shared by the attention kernels.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -16,11 +16,12 @@
 // rotated and stored.  HBM-bound: every byte is read once and written once, with
 // non-temporal loads and stores (cached ones keep lines that are not used again
 // and cost 9% at 40 heads x 128, 10800 tokens: 87.7 us cold, 79.6 us = 5.6 TB/s now;
-// 12 heads, 4680 tokens 18.2 -> 13.8 us).  Between the attention calls of a model's
-// layers the largest of these passes takes longer (72 -> 80 us: its 221 MB used to
-// stay in the 256 MB Infinity Cache) and the attention after it that much less:
-// layers of 40 x 10800, 40 x 4680 and 12 x 4680 tokens take 3925 -> 3928, 807 -> 804 and
-// 260.6 -> 260.1 us (two history-free chunks, alternating).
+// 12 heads, 4680 tokens 18.2 -> 13.8 us).  That holds for tensors that no kernel has
+// just written.  Between the calls of a model's layers the pass gains nothing: the
+// largest takes longer (72 -> 80 us: its 221 MB used to stay in the 256 MB Infinity
+// Cache) and the attention after it that much less.  Layers of 40 x 10800, 40 x 4680,
+// 12 x 4680 and 12 x 1170 tokens take 3821 -> 3827, 802 -> 804, 253.5 -> 252.7 and
+// 47.5 -> 47.9 us (Q, K and V just written, no history; medians, alternating).
 
 #include <hip/hip_runtime.h>
 

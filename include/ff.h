@@ -185,9 +185,10 @@ ff_status ff_anchor_set(ff_cache* cache, int32_t layer, int32_t n_frames, const 
  * cores with float32 accumulation, softmax in float32, probabilities and
  * output rounded to bf16 (nearest even).  f32: float32 throughout.
  * softmax_scale is normally 1/sqrt(head_dim).
- * bf16 launches whose last round of workgroups is partial run that round's
- * work as key parts whose partial results go to a per-stage scratch region
- * of the cache buffer, merged by a second kernel on the same stream: calls of
+ * Small bf16 launches split their keys inside each workgroup.  Larger ones
+ * whose last round of workgroups is partial run that round's work as key parts
+ * whose partial results go to a per-stage scratch region of the cache buffer,
+ * merged by a second kernel on the same stream: calls of
  * one stage (any layer) that overlap in time on different streams race on
  * it, so order them on one stream (different stages are independent), or use
  * ff_chunk_attention_ws with a workspace per concurrent call. */
